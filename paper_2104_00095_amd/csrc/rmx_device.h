@@ -16,10 +16,35 @@ __device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_read
 // defines RMX_GLOBAL_AS away.)
 #ifndef RMX_GLOBAL_AS
 #define RMX_GLOBAL_AS __attribute__((address_space(1)))
+#define RMX_CONST_AS __attribute__((address_space(4)))
+// Product of two integers below 2^23 in magnitude (full rate; a 32-bit product is not).
+__device__ __forceinline__ int mul24(int a, int b) { return __mul24(a, b); }
+#else
+#define RMX_CONST_AS
+inline int mul24(int a, int b) { return a * b; }
 #endif
 template <typename T>
 __device__ __forceinline__ T load_global(const T* p) {
     return *(const RMX_GLOBAL_AS T*)p;
+}
+
+// Data that no thread of the launch writes (descriptors, lists of an earlier kernel), read
+// at addresses that are the same in every lane: through the constant address space the loads
+// are scalar ones, and a value read once stays good across the kernel's stores.  (Generic
+// loads of the descriptors are vector loads, repeated after every store.)
+typedef const RMX_CONST_AS DevSolid DevSolidC;
+__device__ __forceinline__ DevSolidC* const_solid(const DevSolid* solids, int s) {
+    return (DevSolidC*)(solids + s);
+}
+template <typename T>
+__device__ __forceinline__ T load_const(const T* p) {
+    return *(const RMX_CONST_AS T*)p;
+}
+// A double known to be the same in every lane, in scalar registers.
+__device__ __forceinline__ double uniform_double(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)uniform_int((int)b), hi = (unsigned)uniform_int((int)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
 // ------------------------------------------------------------------------------------
@@ -342,23 +367,17 @@ __device__ __forceinline__ void block_scan(int v, int& excl, int& total, int* s_
     __syncthreads();
 }
 
-// Entries [0, count) of a list, split into one contiguous range per XCD in proportion to
-// its share of the grid (workgroups are dealt to the XCDs round-robin): neighbouring
-// entries, whose halos overlap, are then fetched into one L2.  The calling block takes
-// begin, begin + stride, ... below end.
+// Entries [0, count) of a list, split into one contiguous range per XCD (workgroups are
+// dealt to the XCDs round-robin): neighbouring entries, whose halos overlap, are then
+// fetched into one L2.  The calling block takes begin, begin + stride, ... below end.
 struct XcdRange {
     int begin, end, stride;
 };
 __device__ __forceinline__ XcdRange xcd_range(int count) {
-    const int G = gridDim.x, x = blockIdx.x % kXcds;
-    int before = 0;   // blocks on the XCDs dealt before this one
-    for (int y = 0; y < x; ++y) before += (G - y + kXcds - 1) / kXcds;
-    const int mine = (G - x + kXcds - 1) / kXcds;   // >= 1: this block is one of them
-    XcdRange r;
-    r.begin = (int)((int64_t)count * before / G) + (int)blockIdx.x / kXcds;
-    r.end = (int)((int64_t)count * (before + mine) / G);
-    r.stride = mine;
-    return r;
+    const int G = gridDim.x, b = blockIdx.x;
+    if (G < kXcds) return {b, count, G};   // (some XCD would have no block)
+    const int x = b % kXcds, per = (count + kXcds - 1) / kXcds;
+    return {x * per + b / kXcds, min(count, (x + 1) * per), (G - x + kXcds - 1) / kXcds};
 }
 
 // The same value, through an identity lane move the compiler cannot see through: work
@@ -369,7 +388,7 @@ __device__ __forceinline__ int opaque_lane_value(int v) {
 }
 
 // ------------------------------------------------------------------------------------
-// Extrapolation of one layer.  A group of NL = 4, 8 or 16 aligned lanes per band cell.
+// Extrapolation of one layer.  A group of 4, 8 or 16 aligned lanes per band cell.
 // ------------------------------------------------------------------------------------
 
 template <typename T>
@@ -390,12 +409,16 @@ __device__ __forceinline__ void zero(Moments<T>& a) {
     for (int q = 0; q < 5; ++q) a.g[q] = 0;
 }
 
-// Sums over aligned groups of NL lanes (4, 8 or 16) by DPP moves within a row: swap
+// Sums over aligned groups of 4, 8 or 16 lanes by DPP moves within a row: swap
 // neighbours, swap pairs, then mirror the half-row (8) and the row (16).  Every lane of a
 // group ends with the same, commutatively formed, sum.
 template <int CTRL>
 __device__ __forceinline__ int dpp_i(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ int dpp_v(int v) {
+    return dpp_i<CTRL>(v);
 }
 template <int CTRL>
 __device__ __forceinline__ double dpp_v(double v) {
@@ -409,23 +432,26 @@ __device__ __forceinline__ float dpp_v(float v) {
     return __int_as_float(dpp_i<CTRL>(__float_as_int(v)));
 }
 
-template <int NL, int CTRL, typename T>
-__device__ __forceinline__ void reduce_step(Moments<T>& a) {
+template <int CTRL, int N, typename T>
+__device__ __forceinline__ void reduce_step(T* a) {
 #pragma unroll
-    for (int q = 0; q < 10; ++q) a.m[q] += dpp_v<CTRL>(a.m[q]);
-#pragma unroll
-    for (int q = 0; q < 12; ++q) a.r[q] += dpp_v<CTRL>(a.r[q]);
-#pragma unroll
-    for (int q = 0; q < 5; ++q) a.g[q] += dpp_i<CTRL>(a.g[q]);
+    for (int q = 0; q < N; ++q) a[q] += dpp_v<CTRL>(a[q]);
 }
 
-template <int NL, typename T>
-__device__ __forceinline__ void reduce_lanes(Moments<T>& a) {
-    static_assert(NL == 4 || NL == 8 || NL == 16, "lane group");
-    reduce_step<NL, 0xB1>(a);                   // quad_perm [1,0,3,2]
-    reduce_step<NL, 0x4E>(a);                   // quad_perm [2,3,0,1]
-    if (NL >= 8) reduce_step<NL, 0x141>(a);     // row_half_mirror
-    if (NL >= 16) reduce_step<NL, 0x140>(a);    // row_mirror
+// (sh: log2 of the group's lanes, 2, 3 or 4, the same in the whole block)
+template <int N, typename T>
+__device__ __forceinline__ void reduce_values(T* a, int sh) {
+    reduce_step<0xB1, N>(a);                 // quad_perm [1,0,3,2]
+    reduce_step<0x4E, N>(a);                 // quad_perm [2,3,0,1]
+    if (sh >= 3) reduce_step<0x141, N>(a);   // row_half_mirror
+    if (sh >= 4) reduce_step<0x140, N>(a);   // row_mirror
+}
+
+template <typename T>
+__device__ __forceinline__ void reduce_lanes(Moments<T>& a, int sh) {
+    reduce_values<10>(a.m, sh);
+    reduce_values<12>(a.r, sh);
+    reduce_values<5>(a.g, sh);
 }
 
 // Two signed 16-bit sums packed as lo + hi * 2^16 (|sums| < 2^15 for r <= 4).
@@ -456,31 +482,75 @@ __device__ __forceinline__ long long det_gram(const int* gp) {
     return s0 * t5 - s1 * t4 + s2 * t3 + s3 * t2 - s4 * t1 + s5 * t0;
 }
 
-// Intercept of the WLS fit from the normal equations, Cholesky in FP64.
-__device__ __forceinline__ void solve_intercept(const double* M, const double* Rr,
-                                                double out[3]) {
+// 1 / x to within an ulp for x of mid_range magnitude.
+__device__ __forceinline__ double rcp_newton2(double x) {
+    const double y0 = __builtin_amdgcn_rcp(x);
+    const double y1 = fma(y0, fma(-x, y0, 1.0), y0);
+    return fma(y1, fma(-x, y1, 1.0), y1);
+}
+
+// Intercept of the WLS fit of one component from the normal equations M [b0 bx by bz] = R
+// (M as in Moments::m), in FP64.  certain: every pivot is above 1e-4 of its diagonal, so M
+// is certainly not singular where its entries are exact to c u, u the rounding unit of FP64
+// and c about 100: the error of a pivot grows at most by the inverse of the pivots before
+// it, to 100 u 1e8 of the diagonal at the last.
+struct Intercept {
+    double value;
+    bool certain;
+};
+constexpr double kPivotTol = 1e-4;
+
+// FP64 moments: the slopes eliminated from the last on (four reciprocals, no square root).
+__device__ __forceinline__ Intercept solve_eliminate(const double* M, double r0, double r1,
+                                                     double r2, double r3) {
+    const double i3 = rcp_newton2(M[9]);
+    const double f0 = M[3] * i3, f1 = M[6] * i3, f2 = M[8] * i3;
+    const double m0 = fma(-f0, M[3], M[0]), m1 = fma(-f0, M[6], M[1]), m2 = fma(-f0, M[8], M[2]);
+    const double m4 = fma(-f1, M[6], M[4]), m5 = fma(-f1, M[8], M[5]), m7 = fma(-f2, M[8], M[7]);
+    const double p0 = fma(-f0, r3, r0), p1 = fma(-f1, r3, r1), p2 = fma(-f2, r3, r2);
+    const double i2 = rcp_newton2(m7);
+    const double h0 = m2 * i2, h1 = m5 * i2;
+    const double n0 = fma(-h0, m2, m0), n1 = fma(-h0, m5, m1), n4 = fma(-h1, m5, m4);
+    const double q0 = fma(-h0, p2, p0), q1 = fma(-h1, p2, p1);
+    const double k0 = n1 * rcp_newton2(n4);
+    const double k = fma(-k0, n1, n0);
+    return {fma(-k0, q1, q0) / k, M[9] > kPivotTol * M[0] && m7 > kPivotTol * M[7] &&
+                                      n4 > kPivotTol * M[4] && k > kPivotTol * M[0]};
+}
+
+// FP32 moments: Cholesky.  (Their rounding can leave M close to singular, and the value then
+// depends on the way it is solved.)
+__device__ __forceinline__ Intercept solve_cholesky(const double* M, double r0, double r1,
+                                                    double r2, double r3) {
     const double l00 = sqrt(M[0]);
     const double i00 = 1.0 / l00;
     const double l10 = M[1] * i00, l20 = M[2] * i00, l30 = M[3] * i00;
-    const double l11 = sqrt(M[4] - l10 * l10);
+    const double p1 = M[4] - l10 * l10;
+    const double l11 = sqrt(p1);
     const double i11 = 1.0 / l11;
     const double l21 = (M[5] - l20 * l10) * i11, l31 = (M[6] - l30 * l10) * i11;
-    const double l22 = sqrt(M[7] - l20 * l20 - l21 * l21);
+    const double p2 = M[7] - l20 * l20 - l21 * l21;
+    const double l22 = sqrt(p2);
     const double i22 = 1.0 / l22;
     const double l32 = (M[8] - l30 * l20 - l31 * l21) * i22;
-    const double l33 = sqrt(M[9] - l30 * l30 - l31 * l31 - l32 * l32);
+    const double p3 = M[9] - l30 * l30 - l31 * l31 - l32 * l32;
+    const double l33 = sqrt(p3);
     const double i33 = 1.0 / l33;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const double y0 = Rr[c] * i00;
-        const double y1 = (Rr[3 + c] - l10 * y0) * i11;
-        const double y2 = (Rr[6 + c] - l20 * y0 - l21 * y1) * i22;
-        const double y3 = (Rr[9 + c] - l30 * y0 - l31 * y1 - l32 * y2) * i33;
-        const double b3 = y3 * i33;
-        const double b2 = (y2 - l32 * b3) * i22;
-        const double b1 = (y1 - l21 * b2 - l31 * b3) * i11;
-        out[c] = (y0 - l10 * b1 - l20 * b2 - l30 * b3) * i00;
-    }
+    const double y0 = r0 * i00;
+    const double y1 = (r1 - l10 * y0) * i11;
+    const double y2 = (r2 - l20 * y0 - l21 * y1) * i22;
+    const double y3 = (r3 - l30 * y0 - l31 * y1 - l32 * y2) * i33;
+    const double b3 = y3 * i33;
+    const double b2 = (y2 - l32 * b3) * i22;
+    const double b1 = (y1 - l21 * b2 - l31 * b3) * i11;
+    return {(y0 - l10 * b1 - l20 * b2 - l30 * b3) * i00,
+            M[0] > 0.0 && p1 > kPivotTol * M[4] && p2 > kPivotTol * M[7] && p3 > kPivotTol * M[9]};
+}
+
+template <typename T>
+__device__ __forceinline__ Intercept solve_intercept(const double* M, double r0, double r1,
+                                                     double r2, double r3) {
+    return sizeof(T) == 4 ? solve_cholesky(M, r0, r1, r2, r3) : solve_eliminate(M, r0, r1, r2, r3);
 }
 
 // 1 / |d| for |d|^2 = 0..48 (offsets within radius 4).
@@ -509,23 +579,22 @@ struct CellCtx {
     int64_t ncell;
     const double* __restrict__ xi;
     const int8_t* __restrict__ labels;
-    int32_t anchor;               // linear index of the anchor datum
-    double a0, a1, a2;            // its xi
+    double a0, a1, a2;            // xi of the anchor datum
     double g0, g1, g2, rgn;       // normal (unnormalised) and 1/|g / rho|
     const double* rho;            // the solid's spacing ratios; null when they are equal
 };
 
 // Accumulate, from global memory, the moments of the eligible data within Chebyshev
 // radius r (used for radii beyond the staged halo).  The (2r+1)^2 rows (dy, dz) of the box
-// are dealt to the NL lanes of the cell.  Eq. (weight): w = 2^-(|dx|+|dy|+|dz|), times
+// are dealt to the nl lanes of the cell.  Eq. (weight): w = 2^-(|dx|+|dy|+|dz|), times
 // the cosine between x_e - x_d = -(dx rho_x, dy rho_y, dz rho_z) h and the normal when
 // use_normal; data with (dx gx + dy gy) + dz gz >= 0 (that exact expression, no
 // contraction) get weight 0.
-template <int NL, typename T>
+template <typename T>
 __device__ __forceinline__ void gather_any(const CellCtx& cx, int r, bool use_normal, int lq,
-                                        Moments<T>& acc) {
+                                           int nl, Moments<T>& acc) {
     const int D = 2 * r + 1;
-    for (int row = lq; row < D * D; row += NL) {
+    for (int row = lq; row < D * D; row += nl) {
         const int dy = row % D - r, dz = row / D - r;
         const int jj = cx.j + dy, kk = cx.k + dz;
         if ((unsigned)jj >= (unsigned)cx.n1 || (unsigned)kk >= (unsigned)cx.n2) continue;

@@ -38,11 +38,21 @@ constexpr int kDecNoNormal = 64;
 constexpr int kBrick = 8;
 constexpr int kBrickHalo = 2;
 constexpr int kBrickSpan = kBrick + 2 * kBrickHalo;                // 12
-constexpr int kBrickCells = kBrickSpan * kBrickSpan * kBrickSpan;  // 1728
-// LDS of a brick: staged xi (FP64, or FP32 offsets in the reduced-precision form), one
-// state byte per cell, and the list of the brick's layer cells.
+// Staged cells of a brick at most: in FP32 the whole region, in FP64 what lets four blocks per
+// CU fit the LDS.  The layers of smooth surfaces need 650 on average and up to 1250; half a
+// brick at most 1152.
+template <typename T>
+__host__ __device__ constexpr int span_cells() {
+    return sizeof(T) == 4 ? kBrickSpan * kBrickSpan * kBrickSpan : 1440;
+}
+// LDS of a brick: staged xi (FP64, or FP32 offsets in the reduced-precision form), a bit per
+// cell of the brick, a word per row of its region, eight words for the block, and the lists
+// of the staged cells and of the brick's layer cells.
 constexpr size_t brick_lds_bytes(int precision) {
-    return kBrickCells * (3 * (precision == 1 ? 4 : 8) + 1) + 512 * 2;
+    return (precision == 1 ? span_cells<float>() * 3 * 4 : span_cells<double>() * 3 * 8) +
+           8 * kBrick + 4 * kBrickSpan * kBrickSpan + 8 * 4 +
+           2 * (precision == 1 ? span_cells<float>() : span_cells<double>()) +
+           2 * kBrick * kBrick * kBrick;
 }
 
 // One solid as the kernels see it.

@@ -15,11 +15,12 @@
 //               the normals of the brick's cells of that layer by central differences, from
 //               the field before any write.
 //   k_extrap    one launch per layer, ascending: a block stages a listed brick with a
-//               halo of r_s (xi and labels, 12^3 cells, one round trip) in LDS; a group
-//               of 4, 8 or 16 lanes per cell of the layer (as many as keep the brick's
-//               cells in one pass) gathers the (2r+1)^3 box from LDS, accumulates the 4x4
-//               normal-equation moments, reduces them by DPP moves, decides degeneracy by
-//               an exact integer determinant, solves by Cholesky in FP64 and writes xi_e.
+//               halo of r_s (12^3 cells: the labels as row bits, then xi where a fit reads
+//               it) in LDS; a group of 4, 8 or 16 lanes per cell of the layer (as many as
+//               keep the brick's cells in one pass) gathers the (2r+1)^3 box from LDS,
+//               accumulates the 4x4 normal-equation moments, reduces them by DPP moves,
+//               decides degeneracy by an exact integer determinant, solves in FP64 and
+//               writes xi_e.
 // The work is bandwidth- and latency-bound, with 4x4 systems per cell: no MFMA.
 #include "rmx_device.h"
 
@@ -596,95 +597,213 @@ __global__ __launch_bounds__(kLabelThreads) void k_label(Batch b) {
 // ------------------------------------------------------------------------------------
 // Extrapolation of the layer-l cells of one brick, staged in LDS.
 // ------------------------------------------------------------------------------------
-// Staged cell states (one byte per cell of the 12^3 region).
-constexpr uint8_t kStNone = 0;   // carries no data for layer l (outside the box, unmarked,
-                                 // or in layer l or above); its staged xi is 0
-constexpr uint8_t kStData = 1;   // a datum for layer l: label in [0, l)
-constexpr uint8_t kStTarget = 2; // a cell of layer l
-
-// Reciprocal lengths 1/|x'| (in units of the smallest spacing) of the radius-2 offsets:
-// entry (|dx| * 3 + |dy|) * 3 + |dz| is 1 / |(dx rho_x, dy rho_y, dz rho_z)| (eq. (weight)
-// with the spacings of the axes); d == nullptr or equal spacings: 1 / |d|.
+// The weights of the radius-2 offsets: entry (|dx| * 3 + |dy|) * 3 + |dz| is
+// 2^-(|dx|+|dy|+|dz|) / |(dx rho_x, dy rho_y, dz rho_z)| (eq. (weight) with the spacings of
+// the axes); d == nullptr or equal spacings: the same over |d|.
 constexpr int kRlen = 27;
 
-__device__ __forceinline__ double rlen_entry(const DevSolid* d, int e) {
+__device__ __forceinline__ double rlen_entry(DevSolidC* d, int e) {
     const int ax = e / 9, ay = (e / 3) % 3, az = e % 3;
     if (e == 0) return 0.0;
-    if (d == nullptr || !d->aniso) return c_rlen[ax * ax + ay * ay + az * az];
-    return 1.0 / norm3((double)ax * d->rho[0], (double)ay * d->rho[1], (double)az * d->rho[2]);
+    const double r = d == nullptr || !d->aniso
+                         ? c_rlen[ax * ax + ay * ay + az * az]
+                         : 1.0 / norm3((double)ax * d->rho[0], (double)ay * d->rho[1],
+                                       (double)az * d->rho[2]);
+    return ldexp(r, -(ax + ay + az));
 }
 
-// Moments of the eligible data of radius r_s = 2 around staged cell idx.  The staged
-// values are xi - A for the brick's anchor A (0 where the cell carries no data), so a
-// datum enters as w * v with no selection of the value.  A lane takes whole rows
-// (dy, dz); within a row the five data (dx = -2..2) are first summed into row moments
-// (sum w, sum w dx, sum w dx^2, sum w v, sum w dx v), which then update the 4 x 4 normal
-// matrix and the right-hand sides once per row.  Eq. (weight): w = 2^-(|dx|+|dy|+|dz|),
-// times, with the normal, (x_e - x_d).n / |x_e - x_d| where that is positive; the sign
-// is decided on (dx gx + dy gy) + dz gz, in that order, without contraction.  The integer
-// moments of the positive-weight offsets (for the exact rank test) are summed the same way.
-template <int NL, bool NRM, typename T>
-__device__ __forceinline__ void gather_lds(const T* __restrict__ sx,
-                                           const uint8_t* __restrict__ ss,
-                                           const double* __restrict__ s_rlen, int idx,
-                                           double g0, double g1, double g2, double rgn, int lq,
-                                           Moments<T>& acc) {
-    constexpr int S = kBrickSpan, S2 = kBrickSpan * kBrickSpan;
+// Row sums over the five offsets dx = -2..2 for a 5-bit set of them, with the weights
+// w = 2^-|dx|: sum w, sum w dx, sum w dx^2.
+constexpr int kRowSets = 32;
+struct RowSums {
+    double s0, s1, s2;
+};
+struct RowSumTable {
+    RowSums v[kRowSets];
+};
+constexpr RowSumTable make_row_sums() {
+    RowSumTable t{};
+    for (int e = 0; e < kRowSets; ++e)
+        for (int u = 0; u < 5; ++u) {
+            const int dx = u - 2, ad = dx < 0 ? -dx : dx;
+            const double w = ((e >> u) & 1) / (double)(1 << ad);
+            t.v[e].s0 += w;
+            t.v[e].s1 += w * dx;
+            t.v[e].s2 += w * dx * dx;
+        }
+    return t;
+}
+static __constant__ RowSumTable c_row_sums = make_row_sums();
+
+// Tables of the fits in LDS: the weights (of the solid in `tab`, -1: equal spacings) and
+// the row sums.
+struct FitTables {
+    double* rlen;       // [kRlen]
+    RowSums* rows;      // [kRowSets]
+};
+
+__device__ __forceinline__ void fill_fit_tables(const FitTables& t) {
+    const int tid = threadIdx.x;
+    if (tid < kRlen) t.rlen[tid] = rlen_entry(nullptr, tid);
+    if (tid < 3 * kRowSets)
+        reinterpret_cast<double*>(t.rows)[tid] = reinterpret_cast<const double*>(&c_row_sums)[tid];
+}
+
+// LDS of a staged brick (brick_lds_bytes).
+template <typename T>
+struct BrickLds {
+    T* sx;                       // [3][span_cells<T>()] xi - A of the staged cells
+    unsigned long long* target;  // [8] cells of the layer in plane y = 2 + i of the region:
+                                 // bit 8 k + j is column 2 + j of z = 2 + k
+    unsigned* rows;              // [144] the staged rows as the gathers read them
+    int* ctl;                    // [0..2] the first datum of the rows of wave 0, 1, 2,
+                                 // [3..5] their staged cells, [6] cells listed, [7] a cell
+                                 // is left open
+    uint16_t* slots;             // [span_cells<T>()] code of each staged cell, | kCellNeeded
+    uint16_t* cells;             // [512] the layer's cells
+};
+template <typename T>
+__device__ __forceinline__ BrickLds<T> brick_lds(unsigned char* lds) {
+    BrickLds<T> b;
+    b.sx = reinterpret_cast<T*>(lds);
+    b.target = reinterpret_cast<unsigned long long*>(b.sx + 3 * span_cells<T>());
+    b.rows = reinterpret_cast<unsigned*>(b.target + kBrick);
+    b.ctl = reinterpret_cast<int*>(b.rows + kBrickSpan * kBrickSpan);
+    b.slots = reinterpret_cast<uint16_t*>(b.ctl + 8);
+    b.cells = b.slots + span_cells<T>();
+    return b;
+}
+constexpr unsigned kCellNeeded = 0x8000u;   // a staged cell that carries data
+constexpr unsigned kCellOpen = 0x8000u;     // a listed cell that its first fit left open
+
+// A staged row as the gathers read it: bits 0..11 the columns that carry data, above them
+// the staged place of its column 0 (which itself need not be staged), plus 16.
+__device__ __forceinline__ int row_place(unsigned info) { return (int)(info >> 12) - 16; }
+
+// A cell of the 12^3 region in the block's lists: column, row, plane.
+__device__ __forceinline__ unsigned cell_code(int x, int y, int z) {
+    return (unsigned)(x | (y << 4) | (z << 8));
+}
+__device__ __forceinline__ int code_x(unsigned c) { return (int)(c & 15u); }
+__device__ __forceinline__ int code_y(unsigned c) { return (int)((c >> 4) & 15u); }
+__device__ __forceinline__ int code_z(unsigned c) { return (int)((c >> 8) & 15u); }
+
+// The 25 lines (dy, dz) of the radius-2 box, i = 5 (dz + 2) + dy + 2, i / 5 without a division.
+__device__ __forceinline__ int line_dz(int i) { return ((i * 13) >> 6) - 2; }
+__device__ __forceinline__ int line_dy(int i, int dz) { return i - 5 * dz - 12; }
+// The staged row of line i of the cell on staged row `row`.
+__device__ __forceinline__ int line_row(int i, int row) {
+    return row + i + (kBrickSpan - 5) * ((i * 13) >> 6) - 2 * kBrickSpan - 2;
+}
+
+// Sums over a cell's data of radius r_s = 2, plain weights w = 2^-(|dx|+|dy|+|dz|).  A lane
+// takes every nl-th line of the box around the cell at column x of staged row `row`.  The
+// staged values are xi - A for the brick's anchor A, 0 where the cell carries no data, so a
+// line's sums over dx need no selection, and the normal matrix depends only on which of its
+// five cells carry data: five bits of the row, looked up.  Powers of two scale exactly, so
+// factoring the line's weight out changes no rounding, and the matrix is exact.
+template <typename T>
+__device__ __forceinline__ void gather_plain(const T* __restrict__ sx,
+                                             const unsigned* __restrict__ rows,
+                                             const RowSums* __restrict__ row_sums, int x,
+                                             int row, int lq, int nl, Moments<T>& acc) {
+    unsigned info = rows[line_row(lq, row)];
 #pragma unroll 1
-    for (int row = lq; row < 25; row += NL) {
-        const int dy = row % 5 - 2, dz = row / 5 - 2;
-        const int rb = idx + dz * S2 + dy * S;
-        int st[5];
-        T v0[5], v1[5], v2[5];
+    for (int i = lq; i < 25; i += nl) {
+        const int dz = line_dz(i), dy = line_dy(i, dz);
+        const unsigned bits = (info >> (x - 2)) & 31u;
+        const T* p = sx + (row_place(info) + x - 2);
+        info = rows[line_row(min(i + nl, 24), row)];   // the next line's, read ahead
+        if (bits == 0u) continue;   // no data: the line adds zeros
+        const RowSums rs = row_sums[bits];
+        const T fy = (T)dy, fz = (T)dz;
+        const T w = (T)ldexp(1.0, -(abs(dy) + abs(dz))), wy = fy * w, wz = fz * w;
 #pragma unroll
-        for (int u = 0; u < 5; ++u) {
-            const int q = rb + u - 2;
-            st[u] = ss[q];
-            v0[u] = sx[q];
-            v1[u] = sx[kBrickCells + q];
-            v2[u] = sx[2 * kBrickCells + q];
+        for (int c = 0; c < 3; ++c) {
+            const T* v = p + c * span_cells<T>();
+            const T a0 = v[0], a1 = v[1], a2 = v[2], a3 = v[3], a4 = v[4];
+            const T t0 = fma(T(0.25), a4, fma(T(0.5), a3, a2 + fma(T(0.5), a1, T(0.25) * a0)));
+            const T t1 = fma(T(0.5), a4, fma(T(0.5), a3, fma(T(-0.5), a1, T(-0.5) * a0)));
+            acc.r[c] = fma(w, t0, acc.r[c]);
+            acc.r[3 + c] = fma(w, t1, acc.r[3 + c]);
+            acc.r[6 + c] = fma(wy, t0, acc.r[6 + c]);
+            acc.r[9 + c] = fma(wz, t0, acc.r[9 + c]);
         }
-        const int rowi = abs(dy) * 3 + abs(dz);   // s_rlen entry of (0, dy, dz)
-        const double rowbase = ldexp(1.0, -(abs(dy) + abs(dz)));   // 2^-(|dy|+|dz|), exact
-        double ry = 0.0, rz = 0.0;
-        if (NRM) {
+        const T s0 = (T)rs.s0, s1 = (T)rs.s1, s2 = (T)rs.s2;
+        acc.m[0] = fma(w, s0, acc.m[0]);
+        acc.m[1] = fma(w, s1, acc.m[1]);
+        acc.m[2] = fma(wy, s0, acc.m[2]);
+        acc.m[3] = fma(wz, s0, acc.m[3]);
+        acc.m[4] = fma(w, s2, acc.m[4]);
+        acc.m[5] = fma(wy, s1, acc.m[5]);
+        acc.m[6] = fma(wz, s1, acc.m[6]);
+        acc.m[7] = fma(fy * wy, s0, acc.m[7]);
+        acc.m[8] = fma(fz * wy, s0, acc.m[8]);
+        acc.m[9] = fma(fz * wz, s0, acc.m[9]);
+    }
+}
+
+// Adds the offsets dx of a 5-bit set on line (dy, dz) to the integer sums g (as in Moments).
+__device__ __forceinline__ void add_offsets(int* g, unsigned set, int dy, int dz) {
+    const int ends = __builtin_popcount(set & 17u), mids = __builtin_popcount(set & 10u);
+    const int n = __builtin_popcount(set), nxx = mids + 4 * ends;
+    const int nx = (__builtin_popcount(set & 24u) + __builtin_popcount(set & 16u)) -
+                   (__builtin_popcount(set & 3u) + __builtin_popcount(set & 1u));
+    const int ny = mul24(dy, n), nz = mul24(dz, n);
+    g[0] += n + (nxx << 16);
+    g[1] += nx + (mul24(dy, nx) << 16);
+    g[2] += ny + (mul24(dz, nx) << 16);
+    g[3] += nz + (mul24(dy, ny) << 16);
+    g[4] += mul24(dy, nz) + (mul24(dz, nz) << 16);
+}
+
+// The same with the normal factor: 2^-(|dx|+|dy|+|dz|) (x_e - x_d).n / |x_e - x_d| where that
+// is positive; the sign is decided on (dx gx + dy gy) + dz gz, in that order, without
+// contraction.  In FP64 the weights stay unnormalised (all of a cell's weights share the
+// factor rgn = 1/|g|, which cancels in the fit); the FP32 sums take them normalised.
+template <typename T>
+__device__ __forceinline__ void gather_normal(const T* __restrict__ sx,
+                                              const unsigned* __restrict__ rows,
+                                              const double* __restrict__ rlen, int x, int row,
+                                              double g0, double g1, double g2, double rgn,
+                                              int lq, int nl, Moments<T>& acc) {
+    unsigned info = rows[line_row(lq, row)];
+#pragma unroll 1
+    for (int i = lq; i < 25; i += nl) {
+        const int dz = line_dz(i), dy = line_dy(i, dz);
+        const unsigned bits = (info >> (x - 2)) & 31u;
+        const T* p = sx + (row_place(info) + x - 2);
+        info = rows[line_row(min(i + nl, 24), row)];   // the next line's, read ahead
+        if (bits == 0u) continue;   // no data: the line adds zeros
+        const int rowi = abs(dy) * 3 + abs(dz);
+        T w[5];
+        unsigned pos = 0u;   // the offsets of positive weight
+        {
 #pragma clang fp contract(off)
-            ry = (double)dy * g1;
-            rz = (double)dz * g2;
-        }
-        T s0 = T(0), s1 = T(0), s2 = T(0);
-        T t0[3] = {T(0), T(0), T(0)}, t1[3] = {T(0), T(0), T(0)};
-        int n = 0, nx = 0, nxx = 0;
+            const double ry = (double)dy * g1, rz = (double)dz * g2;
+            const double cw[3] = {rlen[rowi], rlen[9 + rowi], rlen[18 + rowi]};
 #pragma unroll
-        for (int u = 0; u < 5; ++u) {
-            const int dx = u - 2;
-            bool e = st[u] == kStData;
-            double ww = rowbase * (dx == 0 ? 1.0 : (dx == 1 || dx == -1 ? 0.5 : 0.25));
-            if (NRM) {
-#pragma clang fp contract(off)
+            for (int u = 0; u < 5; ++u) {
+                const int dx = u - 2;
                 const double dot = ((double)dx * g0 + ry) + rz;
-                e = e && (dot < 0.0);
-                ww = (-dot * s_rlen[abs(dx) * 9 + rowi] * rgn) * ww;
+                const bool e = ((bits >> u) & 1u) && dot < 0.0;
+                double ww = -dot * cw[abs(dx)];
+                if (sizeof(T) == 4) ww = ww * rgn;
+                w[u] = e ? (T)ww : T(0);
+                pos |= e ? 1u << u : 0u;
             }
-            const T w = e ? (T)ww : T(0);
-            s0 += w;
-            t0[0] = fma(w, v0[u], t0[0]);
-            t0[1] = fma(w, v1[u], t0[1]);
-            t0[2] = fma(w, v2[u], t0[2]);
-            if (dx != 0) {   // resolved at compile time (the loop is unrolled)
-                const T wx = (T)dx * w;
-                s1 += wx;
-                s2 = fma((T)dx, wx, s2);
-                t1[0] = fma(wx, v0[u], t1[0]);
-                t1[1] = fma(wx, v1[u], t1[1]);
-                t1[2] = fma(wx, v2[u], t1[2]);
-            }
-            const int ei = e ? 1 : 0;
-            n += ei;
-            nx += ei * dx;
-            nxx += ei * dx * dx;
         }
         const T fy = (T)dy, fz = (T)dz;
+        T s0 = T(0), s1 = T(0), s2 = T(0);
+#pragma unroll
+        for (int u = 0; u < 5; ++u) {
+            s0 += w[u];
+            if (u != 2) {
+                const T wx = (T)(u - 2) * w[u];
+                s1 += wx;
+                s2 = fma((T)(u - 2), wx, s2);
+            }
+        }
         acc.m[0] += s0;
         acc.m[1] += s1;
         acc.m[2] = fma(fy, s0, acc.m[2]);
@@ -697,265 +816,475 @@ __device__ __forceinline__ void gather_lds(const T* __restrict__ sx,
         acc.m[9] = fma(fz * fz, s0, acc.m[9]);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            acc.r[c] += t0[c];
-            acc.r[3 + c] += t1[c];
-            acc.r[6 + c] = fma(fy, t0[c], acc.r[6 + c]);
-            acc.r[9 + c] = fma(fz, t0[c], acc.r[9 + c]);
+            const T* v = p + c * span_cells<T>();
+            T t0 = T(0), t1 = T(0);
+#pragma unroll
+            for (int u = 0; u < 5; ++u) {
+                t0 = fma(w[u], v[u], t0);
+                if (u != 2) t1 = fma((T)(u - 2) * w[u], v[u], t1);
+            }
+            acc.r[c] += t0;
+            acc.r[3 + c] += t1;
+            acc.r[6 + c] = fma(fy, t0, acc.r[6 + c]);
+            acc.r[9 + c] = fma(fz, t0, acc.r[9 + c]);
         }
-        acc.g[0] += n + (nxx << 16);
-        acc.g[1] += nx + ((dy * nx) << 16);
-        acc.g[2] += dy * n + ((dz * nx) << 16);
-        acc.g[3] += dz * n + ((dy * dy * n) << 16);
-        acc.g[4] += dy * dz * n + ((dz * dz * n) << 16);
+        if (sizeof(T) == 4) add_offsets(acc.g, pos, dy, dz);
     }
 }
 
-// The fits of the compacted layer-l cells of a staged brick, NL lanes per cell.  Values
-// are relative to the brick's anchor A: xi_e = A + the fitted intercept.
-template <int NL, typename T>
-__device__ __forceinline__ void fit_cells(const Batch& b, const DevSolid* d,
-                                          unsigned long long* st, int l, int ox, int oy, int oz,
-                                          int total, unsigned char* lds, const double* s_rlen,
-                                          const double* s_anchor) {
-    const T* sx = reinterpret_cast<const T*>(lds);
-    const uint8_t* ss = reinterpret_cast<const uint8_t*>(lds + kBrickCells * 3 * sizeof(T));
-    const uint16_t* cells =
-        reinterpret_cast<const uint16_t*>(lds + kBrickCells * (3 * sizeof(T) + 1));
-    const int n0 = d->n0, n1 = d->n1, n2 = d->n2;
+// What the fits need of the call.
+struct FitArgs {
+    const DevSolid* solids;
+    unsigned long long* stats;
+    int normal_layers, r_s, r_max;
+};
+// A list entry: the solid and the brick's place.
+__device__ __forceinline__ int entry_solid(unsigned long long pk) { return (int)(pk >> 32); }
+__device__ __forceinline__ int entry_x(unsigned long long pk) { return (int)(pk & 1023ull); }
+__device__ __forceinline__ int entry_y(unsigned long long pk) { return (int)((pk >> 10) & 1023ull); }
+__device__ __forceinline__ int entry_z(unsigned long long pk) { return (int)((pk >> 20) & 1023ull); }
+
+// What a fit needs of its brick: the box index of the region's cell 0 (which may lie outside
+// the box), the row and plane strides, the cells of the box, and the anchor.
+struct BrickCtx {
+    int ox, oy, oz, origin, n0, n01;
+    int64_t nc;
+    double A[3];
+};
+__device__ __forceinline__ int brick_cell(const BrickCtx& c, unsigned q) {
+    return c.origin + code_z(q) * c.n01 + code_y(q) * c.n0 + code_x(q);
+}
+
+// The open cells of a brick's list: radii r_s..r_max with eq. (weight), then F1 (normal
+// factor dropped) at r_max, then F2 (kernel-weighted mean) at r_max, gathered from global
+// memory, each radius accepted by the exact rank test.  A cell fitted from the staged data
+// (`staged`) keeps that value where its r_s data turn out to have full rank.  Rare (nearly
+// degenerate cells, cells whose radius grows, or r_s other than the staged radius), and out
+// of line after the other cells, so that its registers are not the fits'.
+template <typename T>
+static __device__ __noinline__ void fit_open_cells(FitArgs b, unsigned long long pk, int l,
+                                                   unsigned char* lds, int sh, bool staged,
+                                                   double A0, double A1, double A2) {
+    const BrickLds<T> B = brick_lds<T>(lds);
+    const uint16_t* cells = B.cells;
+    const int total = B.ctl[6], r_s = b.r_s, r_max = b.r_max;
+    const bool nrm = l <= b.normal_layers;
+    DevSolidC* d = const_solid(b.solids, entry_solid(pk));
+    unsigned long long* st = b.stats + (int64_t)entry_solid(pk) * kStatWords;
+    const int ox = kBrick * entry_x(pk) - kBrickHalo, oy = kBrick * entry_y(pk) - kBrickHalo,
+              oz = kBrick * entry_z(pk) - kBrickHalo;
+    const int lq = threadIdx.x & ((1 << sh) - 1);
     const int64_t nc = d->ncell;
-    const double* __restrict__ xi = d->xi;
-    const int8_t* __restrict__ labels = d->labels;
-    const int grp = threadIdx.x / NL, lq = threadIdx.x % NL;
-    const double* rho = d->aniso ? d->rho : nullptr;
-    for (int ci = grp; ci < total; ci += 256 / NL) {
-        const int idx = cells[ci];
-        const int x = idx % kBrickSpan, y = (idx / kBrickSpan) % kBrickSpan,
-                  z = idx / (kBrickSpan * kBrickSpan);
+    for (int ci = threadIdx.x >> sh; ci < total; ci += 256 >> sh) {
+        const unsigned q = cells[ci];
+        if (!(q & kCellOpen)) continue;   // (the same in every lane of the cell)
         CellCtx cx;
-        cx.i = ox + x;
-        cx.j = oy + y;
-        cx.k = oz + z;
-        cx.n0 = n0;
-        cx.n1 = n1;
-        cx.n2 = n2;
+        cx.i = ox + code_x(q);
+        cx.j = oy + code_y(q);
+        cx.k = oz + code_z(q);
+        cx.n0 = d->n0;
+        cx.n1 = d->n1;
+        cx.n2 = d->n2;
         cx.le = l;
         cx.ncell = nc;
-        cx.xi = xi;
-        cx.labels = labels;
-        const int32_t cell = (cx.k * n1 + cx.j) * n0 + cx.i;
-        const bool nrm = l <= b.normal_layers;
-        double gn0 = 0.0, gn1 = 0.0, gn2 = 0.0;
-        if (nrm) {   // issued first: the only global loads of the cell
-            gn0 = d->normals[cell];
-            gn1 = d->normals[nc + cell];
-            gn2 = d->normals[2 * nc + cell];
-        }
-        cx.anchor = cell;
-        cx.g0 = gn0;
-        cx.g1 = gn1;
-        cx.g2 = gn2;
-        cx.rgn = 0.0;
-        cx.rho = rho;
-        const bool has_normal = nrm && (gn0 != 0.0 || gn1 != 0.0 || gn2 != 0.0);
-        // the physical gradient is g / rho up to a common factor (1 / h)
-        if (has_normal)
-            cx.rgn = rho ? rlen_scaled(d->irho, gn0, gn1, gn2) : 1.0 / norm3(gn0, gn1, gn2);
-        const bool no_normal = nrm && !has_normal;
-
-        // Passes: radii r_s..r_max with eq. (weight), then F1 (normal factor dropped) at
-        // r_max, then F2 (kernel-weighted mean) at r_max.
+        cx.xi = d->xi;
+        cx.labels = d->labels;
+        cx.a0 = A0;
+        cx.a1 = A1;
+        cx.a2 = A2;
+        const int32_t cell = (cx.k * d->n1 + cx.j) * d->n0 + cx.i;
+        cx.g0 = nrm ? load_global(d->normals + cell) : 0.0;
+        cx.g1 = nrm ? load_global(d->normals + nc + cell) : 0.0;
+        cx.g2 = nrm ? load_global(d->normals + 2 * nc + cell) : 0.0;
+        const bool has_normal = cx.g0 != 0.0 || cx.g1 != 0.0 || cx.g2 != 0.0;
+        cx.rho = d->aniso ? (const double*)d->rho : nullptr;
+        cx.rgn = !has_normal ? 0.0
+                 : d->aniso  ? rlen_scaled((const double*)d->irho, cx.g0, cx.g1, cx.g2)
+                             : 1.0 / norm3(cx.g0, cx.g1, cx.g2);
         int code = -1;
         double res[3] = {0.0, 0.0, 0.0};
-        const int nfit = b.r_max - b.r_s + 1;
-        for (int pass = 0; pass <= nfit + 1; ++pass) {
-            const bool f1 = pass == nfit, f2 = pass == nfit + 1;
+        for (int r = r_s; code < 0; ++r) {   // r_max + 1: F1, r_max + 2: F2
+            const bool f1 = r == r_max + 1, f2 = r > r_max + 1;
             if (f1 && !has_normal) continue;
-            const int r = (f1 || f2) ? b.r_max : b.r_s + pass;
-            const bool un = has_normal && !f1 && !f2;
             Moments<T> acc;
             zero(acc);
-            if (r == kBrickHalo) {
-                if (un)
-                    gather_lds<NL, true, T>(sx, ss, s_rlen, idx, cx.g0, cx.g1, cx.g2, cx.rgn, lq,
-                                            acc);
-                else
-                    gather_lds<NL, false, T>(sx, ss, s_rlen, idx, 0.0, 0.0, 0.0, 0.0, lq, acc);
-            } else {
-                cx.a0 = s_anchor[0];
-                cx.a1 = s_anchor[1];
-                cx.a2 = s_anchor[2];
-                gather_any<NL, T>(cx, r, un, lq, acc);
-            }
-            reduce_lanes<NL>(acc);
+            gather_any<T>(cx, min(r, r_max), has_normal && r <= r_max, lq, 1 << sh, acc);
+            reduce_lanes(acc, sh);
             if (f2) {
                 const double sw = (double)acc.m[0];
-                res[0] = (double)acc.r[0] / sw;
-                res[1] = (double)acc.r[1] / sw;
-                res[2] = (double)acc.r[2] / sw;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) res[c] = (double)acc.r[c] / sw;
                 code = kDecF2;
-                break;
-            }
-            if (det_gram(acc.g) > 0) {
-                double M[10], Rr[12];
+            } else if (det_gram(acc.g) > 0) {
+                double M[10];
 #pragma unroll
-                for (int q = 0; q < 10; ++q) M[q] = (double)acc.m[q];
+                for (int p = 0; p < 10; ++p) M[p] = (double)acc.m[p];
 #pragma unroll
-                for (int q = 0; q < 12; ++q) Rr[q] = (double)acc.r[q];
-                solve_intercept(M, Rr, res);
+                for (int c = 0; c < 3; ++c)
+                    res[c] = solve_intercept<T>(M, (double)acc.r[c], (double)acc.r[3 + c],
+                                                (double)acc.r[6 + c], (double)acc.r[9 + c])
+                                 .value;
                 code = f1 ? kDecF1 : r;
-                break;
             }
         }
         if (lq == 0) {
-            d->xi[cell] = s_anchor[0] + res[0];
-            d->xi[nc + cell] = s_anchor[1] + res[1];
-            d->xi[2 * nc + cell] = s_anchor[2] + res[2];
-            if (d->decisions) d->decisions[cell] = (int8_t)(code + (no_normal ? kDecNoNormal : 0));
+            if (!(staged && code == r_s)) {
+                d->xi[cell] = A0 + res[0];
+                d->xi[nc + cell] = A1 + res[1];
+                d->xi[2 * nc + cell] = A2 + res[2];
+            }
+            if (d->decisions)
+                d->decisions[cell] = (int8_t)(code + (nrm && !has_normal ? kDecNoNormal : 0));
             if (code == kDecF1) atomicAdd(st + ST_F1, 1ull);
             if (code == kDecF2) atomicAdd(st + ST_F2, 1ull);
-            if (code == kDecF1 || code == kDecF2 || code > b.r_s) atomicAdd(st + ST_GROWN, 1ull);
+            if (code > r_s) atomicAdd(st + ST_GROWN, 1ull);   // (the F codes are larger)
         }
     }
 }
 
+// The fits of the listed layer-l cells of a staged brick at the staged radius, 2^sh lanes
+// per cell; a cell whose data may not have full rank is left open (flagged in the list, and
+// ctl[7] set).  Values are relative to the brick's anchor A: xi_e = A + the fitted intercept.
+// (fn0, fn1, fn2): the normal of the group's first cell, loaded while the brick was staged.
+//
+// The rank is certain where the elimination's pivots are: the plain weights' matrix is exact,
+// and so is, to rounding, the FP64 matrix with the normal factor.  The FP32 one is not, so
+// it carries the exact integer Gram matrix of the offsets beside it.
 template <typename T>
-__device__ __forceinline__ void extrap_brick(const Batch& b, int s, unsigned long long* st,
-                                             int l, int bx, int by, int bz,
-                                             unsigned char* lds, int* s_wave,
-                                             double* s_anchor, double* s_rlen, int& tab) {
-    const DevSolid* d = b.solids + s;
-    // the table this brick needs (read before the staging, off the barriers' path)
-    const int want = d->aniso ? s : -1;
-    T* sx = reinterpret_cast<T*>(lds);
-    uint8_t* ss = reinterpret_cast<uint8_t*>(lds + kBrickCells * 3 * sizeof(T));
-    uint16_t* cells = reinterpret_cast<uint16_t*>(lds + kBrickCells * (3 * sizeof(T) + 1));
+__device__ __forceinline__ void fit_cells(DevSolidC* d, bool nrm, const BrickCtx& cx, int total,
+                                          int sh, const BrickLds<T>& B, const FitTables& tab,
+                                          double fn0, double fn1, double fn2) {
+    double* xi = d->xi;
+    int8_t* decisions = d->decisions;
+    const double* normals = d->normals;
+    const int nl = 1 << sh;
+    const int grp = threadIdx.x >> sh, lq = threadIdx.x & (nl - 1);
+    for (int ci = grp; ci < total; ci += 256 >> sh) {
+        const unsigned q = B.cells[ci];
+        const int x = code_x(q), row = code_z(q) * kBrickSpan + code_y(q);
+        const int cell = brick_cell(cx, q);
+        double g0 = fn0, g1 = fn1, g2 = fn2;
+        if (nrm && ci != grp) {
+            g0 = load_global(normals + cell);
+            g1 = load_global(normals + cx.nc + cell);
+            g2 = load_global(normals + 2 * cx.nc + cell);
+        }
+        const bool has_normal = nrm && (g0 != 0.0 || g1 != 0.0 || g2 != 0.0);
+        Moments<T> acc;
+        zero(acc);
+        bool full = true;   // the data have full rank, where the pivots do not tell
+        if (has_normal) {
+            // the physical gradient is g / rho up to a common factor (1 / h)
+            double rgn = 0.0;
+            if (sizeof(T) == 4)
+                rgn = d->aniso ? rlen_scaled((const double*)d->irho, g0, g1, g2)
+                               : 1.0 / norm3(g0, g1, g2);
+            gather_normal<T>(B.sx, B.rows, tab.rlen, x, row, g0, g1, g2, rgn, lq, nl, acc);
+            if (sizeof(T) == 4) {
+                reduce_values<5>(acc.g, sh);
+                full = det_gram(acc.g) > 0;
+            }
+        } else {
+            gather_plain<T>(B.sx, B.rows, tab.rows, x, row, lq, nl, acc);
+        }
+        reduce_values<10>(acc.m, sh);
+        reduce_values<12>(acc.r, sh);
+        // lanes 0..2 of the group solve and store a component each
+        const int comp = min(lq & 3, 2);
+        double M[10], R[4];
+#pragma unroll
+        for (int p = 0; p < 10; ++p) M[p] = (double)acc.m[p];
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            R[p] = (double)(comp == 0 ? acc.r[3 * p]
+                                      : comp == 1 ? acc.r[3 * p + 1] : acc.r[3 * p + 2]);
+        const Intercept f = solve_intercept<T>(M, R[0], R[1], R[2], R[3]);
+        if (lq < 3)
+            xi[comp * cx.nc + cell] = (comp == 0 ? cx.A[0] : (comp == 1 ? cx.A[1] : cx.A[2])) +
+                                      f.value;
+        if (lq == 0) {
+            if (sizeof(T) == 4 && has_normal ? full : f.certain) {
+                if (decisions)
+                    decisions[cell] =
+                        (int8_t)(kBrickHalo + (nrm && !has_normal ? kDecNoNormal : 0));
+            } else {
+                B.cells[ci] = (uint16_t)(q | kCellOpen);
+                B.ctl[7] = 1;
+            }
+        }
+    }
+}
+
+// The 12 labels of a staged row as bits: data (label in [0, l)) and cells of layer l.  base:
+// the box index of the row's column 0, which may lie before the box row's first cell;
+// columns outside [0, n0) give no bit.  One 16-byte load at any alignment holds the row and
+// two labels more on each side (so that the address is a multiple of 4 where n0 is); near
+// the ends of the array the window is moved inside it and the bits shifted back.
+struct RowBits {
+    unsigned data, target;
+};
+struct __attribute__((packed, aligned(1))) Labels16 {
+    uint32_t w[4];
+};
+
+// Bits 7, 15, 23, 31 of x as a nibble (the products never overlap in bits 21..24).
+__device__ __forceinline__ unsigned high_bits(unsigned x) {
+    return (((x & 0x80808080u) >> 7) * 0x00204081u >> 21) & 15u;
+}
+
+__device__ __forceinline__ RowBits label_row_bits(const int8_t* __restrict__ labels, int nc,
+                                                  int base, int ox, int n0, int l) {
+    const int lo = max(0, -ox), hi = min(kBrickSpan, n0 - ox);
+    const unsigned valid = ((1u << hi) - 1u) & ~((1u << lo) - 1u);
+    unsigned below = 0u, upto = 0u;   // labels in [0, l) and in [0, l], bit i: column i
+    if (nc >= 16) {
+        const int a = base - 2, w = min(max(a, 0), nc - 16);
+        const auto* v = (const RMX_GLOBAL_AS Labels16*)(labels + w);
+        // (b | 0x80) - l has its high bit clear only where b < l: -1 is 255, and no byte
+        // borrows from the next
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const unsigned q = v->w[u] | 0x80808080u;
+            below |= high_bits(~(q - 0x01010101u * (unsigned)l)) << (4 * u);
+            upto |= high_bits(~(q - 0x01010101u * (unsigned)(l + 1))) << (4 * u);
+        }
+        // column j lies at window place a - w + 2 + j, with -4 <= a - w <= 11
+        below = (below << 2) >> (a - w + 4);
+        upto = (upto << 2) >> (a - w + 4);
+    } else {
+        for (int j = lo; j < hi; ++j) {
+            const int lab = load_global(labels + base + j);
+            below |= (lab >= 0 && lab < l) ? 1u << j : 0u;
+            upto |= (lab >= 0 && lab <= l) ? 1u << j : 0u;
+        }
+    }
+    return {below & valid, upto & ~below & valid};
+}
+
+// A brick is bound by the latency of its dependent loads and by the instructions of its
+// fits, not by bandwidth.  It takes two round trips: the labels (one 16-byte load per row),
+// then xi of the cells that some fit reads -- the data within radius 2 of a cell of the
+// layer, about 250 of the region's 1728 -- with the normals of the groups' first cells.
+// Staged are, row by row, the columns from the first to the last within radius 2 of a cell
+// of the layer (about 650 cells; 0 where they carry no data), so that a gather reads five
+// consecutive places of a row and the block's LDS leaves room for four blocks per CU.  A
+// brick whose columns exceed the staged places (layers around solids of a few cells; not
+// in FP32, whose places hold the whole region) is staged and fitted in two halves along z
+// (kHalf, `half`), whose columns always fit.
+//
+// Of a block's 13 us on a 256^3 sphere (layers past the normal's; wall-clock stamps) the
+// gathers take 2.6 (4.2 with the normal factor), the labels' round trip 1.0, xi's 1.2, the
+// lists of rows and cells 2.0, the reduction and solve 1.1.  Staging all 1728 cells with
+// their labels as bytes (1 round trip, 41 MB a launch), moments summed per datum and a rank
+// test on every cell took 22: a layer's launch went 23.4 -> 15 us there and 38 -> 25 us on a
+// suspension of 40 ellipsoids.  Measured slower: the rows of a brick along the axis that
+// gives its gathers the fewest lines (fewer lines, but 0.6 us more to transpose the bits:
+// call 144 -> 161 us), and a row's xi loaded by the thread that owns the row, without the
+// list of staged cells (three round trips instead of one: 144 -> 158 us).
+template <typename T>
+static __device__ __noinline__ void finish_brick(FitArgs b, unsigned long long pk, int l,
+                                                 unsigned char* lds, FitTables tables, int sh,
+                                                 double A0, double A1, double A2);
+
+template <typename T, bool kHalf>
+__device__ __forceinline__ void extrap_brick(const FitArgs& b, unsigned long long pk, int l,
+                                             unsigned char* lds, const FitTables& tables,
+                                             int& tab, int half) {
+    constexpr int S = kBrickSpan, S2 = kBrickSpan * kBrickSpan;
+    const int s = entry_solid(pk);
+    DevSolidC* d = const_solid(b.solids, s);
+    const int want = d->aniso ? s : -1;   // the weight table this brick needs
+    const BrickLds<T> B = brick_lds<T>(lds);
     // re-derived per brick: the staging index math is not kept live across bricks
     const int tid = opaque_lane_value(threadIdx.x);
-    const int lane = tid & 63, wid = tid >> 6;
-    const int n0 = d->n0, n1 = d->n1, n2 = d->n2;
-    const int64_t nc = d->ncell;
-    const double* __restrict__ xi = d->xi;
-    const int8_t* __restrict__ labels = d->labels;
-    const int ox = kBrick * bx - kBrickHalo, oy = kBrick * by - kBrickHalo,
-              oz = kBrick * bz - kBrickHalo;
-    // Stage labels and xi of the 12^3 cells.  All loads of the thread are issued before
-    // its first LDS store (the stores cannot be moved above them), so the staging costs
-    // one round trip.  A cell outside the box loads cell 0 of the box, always there, and
-    // is replaced by "no data": no load waits on a branch.
-    // The labels are loaded first: the anchor search below needs only them (loads
-    // complete in issue order), so it overlaps the xi loads still in flight.
-    constexpr int kH = (kBrickCells + 255) / 256;
-    int lraw[kH];  // the label loaded (cell 0's outside the box)
-    int cidx[kH];  // the cell loaded (0 outside the box)
-    unsigned inmask = 0u;   // bit h: cell h of the thread lies in the box
-    double v0[kH], v1[kH], v2[kH];
-#pragma unroll
-    for (int h = 0; h < kH; ++h) {
-        const int q = tid + 256 * h;
-        const int x = q % kBrickSpan, y = (q / kBrickSpan) % kBrickSpan,
-                  z = q / (kBrickSpan * kBrickSpan);
-        const int gx = ox + x, gy = oy + y, gz = oz + z;
-        const bool in = q < kBrickCells && (unsigned)gx < (unsigned)n0 &&
-                        (unsigned)gy < (unsigned)n1 && (unsigned)gz < (unsigned)n2;
-        cidx[h] = in ? (gz * n1 + gy) * n0 + gx : 0;
-        inmask |= in ? 1u << h : 0u;
-        lraw[h] = load_global(labels + cidx[h]);
+    const int lane = tid & 63, wid = uniform_int(tid >> 6);
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    const int n1 = d->n1, n2 = d->n2;
+    BrickCtx cx;
+    cx.n0 = d->n0;
+    cx.n01 = cx.n0 * n1;
+    cx.nc = d->ncell;
+    cx.ox = kBrick * entry_x(pk) - kBrickHalo;
+    cx.oy = kBrick * entry_y(pk) - kBrickHalo;
+    cx.oz = kBrick * entry_z(pk) - kBrickHalo;
+    cx.origin = cx.oz * cx.n01 + cx.oy * cx.n0 + cx.ox;
+    const double* xi = d->xi;
+    // Waves 0..2, a row per thread (threads past the last: empty rows).
+    const int ry = tid % S, rz = tid / S;
+    unsigned data = 0u;
+    if (wid < 3) {
+        RowBits rb = {0u, 0u};
+        if (tid < S2 && (unsigned)(cx.oy + ry) < (unsigned)n1 &&
+            (unsigned)(cx.oz + rz) < (unsigned)n2)
+            rb = label_row_bits(d->labels, (int)cx.nc, cx.origin + rz * cx.n01 + ry * cx.n0,
+                                cx.ox, cx.n0, l);
+        data = rb.data;
+        const int yc = ry - kBrickHalo, zc = rz - kBrickHalo;
+        if ((unsigned)yc < (unsigned)kBrick && (unsigned)zc < (unsigned)kBrick)
+            reinterpret_cast<uint8_t*>(B.target)[yc * kBrick + zc] =
+                (uint8_t)(rb.target >> kBrickHalo);
+        // the first datum of the wave's rows
+        const unsigned long long m = __ballot(data != 0u);
+        if (m ? lane == __builtin_ctzll(m) : lane == 0)
+            B.ctl[wid] = m ? (int)cell_code(__builtin_ctz(data), ry, rz) : -1;
     }
-#pragma unroll
-    for (int h = 0; h < kH; ++h) {
-        const int c = cidx[h];
-        v0[h] = load_global(xi + c);
-        v1[h] = load_global(xi + nc + c);
-        v2[h] = load_global(xi + 2 * nc + c);
-    }
-    // nothing that uses a loaded label may be scheduled above the xi loads
-    __builtin_amdgcn_sched_barrier(0);
-    int lbv[kH];   // the cell's label, -1 outside the box
-#pragma unroll
-    for (int h = 0; h < kH; ++h) lbv[h] = (inmask >> h) & 1u ? lraw[h] : -1;
-    // The brick's anchor A: xi of the first staged cell (in staging order) that carries
-    // data for layer l; one exists, since every layer-l cell has a face neighbour in layer
-    // l - 1.  Staged values are xi - A: the fit is invariant to the shift, and the
-    // offsets are small (the region spans 12 cells), which keeps the moments accurate and
-    // lets the reduced-precision form hold them in FP32.
-    // (The wave's first such cell: staged cells q = tid + 256 h are in order of h first,
-    // so it is the lowest lane of the first slot h whose ballot is not empty.)
-    int qf = 0x7fffffff;
-#pragma unroll
-    for (int h = kH - 1; h >= 0; --h) {
-        const unsigned long long m = __ballot(lbv[h] >= 0 && lbv[h] < l);
-        if (m) qf = 256 * h + 64 * wid + __builtin_ctzll(m);
-    }
-    if (lane == 0) s_wave[wid] = qf;
-    __syncthreads();
-    // the reciprocal-length table of the solid's spacings, when another one is loaded
-    // (uniform: the table's owner is the same in every thread)
-    if (want != tab) {
-        if (tid < kRlen) s_rlen[tid] = rlen_entry(d, tid);
+    if (want != tab) {   // uniform: the table's owner is the same in every thread
+        if (tid < kRlen) tables.rlen[tid] = rlen_entry(d, tid);
         tab = want;
     }
-    const int qa = min(min(s_wave[0], s_wave[1]), min(s_wave[2], s_wave[3]));
-    if (qa != 0x7fffffff && (qa & 255) == tid) {
-#pragma unroll
-        for (int h = 0; h < kH; ++h)
-            if (h == (qa >> 8)) {
-                s_anchor[0] = v0[h];
-                s_anchor[1] = v1[h];
-                s_anchor[2] = v2[h];
-            }
-    }
-    if (qa == 0x7fffffff && tid == 0) s_anchor[0] = s_anchor[1] = s_anchor[2] = 0.0;
     __syncthreads();
-    const double A0 = s_anchor[0], A1 = s_anchor[1], A2 = s_anchor[2];
+    int width = 0, lo = 0, place = 0;
+    unsigned near = 0u;
+    if (wid < 3) {
+        // The columns within radius 2 of a cell of the layer: the planes y within 2 (the
+        // nearest one twice where one would lie outside), their rows z within 2, then two
+        // columns to each side.
+        if (tid < S2) {
+            const int yc = ry - kBrickHalo, zs = 8 * (rz - 2 * kBrickHalo);
+            unsigned long long t = 0ull;
 #pragma unroll
-    for (int h = 0; h < kH; ++h) {
-        const int q = tid + 256 * h;
-        if (q < kBrickCells) {
-            const bool data = lbv[h] >= 0 && lbv[h] < l;
-            ss[q] = data ? kStData : (lbv[h] == l ? kStTarget : kStNone);
-            sx[q] = data ? (T)(v0[h] - A0) : T(0);
-            sx[kBrickCells + q] = data ? (T)(v1[h] - A1) : T(0);
-            sx[2 * kBrickCells + q] = data ? (T)(v2[h] - A2) : T(0);
+            for (int dy = -2; dy <= 2; ++dy) t |= B.target[min(max(yc + dy, 0), kBrick - 1)];
+            if (kHalf) t &= half ? 0xFFFFFFFF00000000ull : 0x00000000FFFFFFFFull;
+            t = (zs >= 0 ? t >> zs : t << -zs) & 0xFFFFFFFFFFull;   // five rows
+            t |= t >> 32;
+            near = (unsigned)(t | t >> 8 | t >> 16 | t >> 24) & 255u;
+            near <<= kBrickHalo;
+            near |= (near << 1) | (near >> 1) | (near << 2) | (near >> 2);
+            lo = near ? __builtin_ctz(near) : 0;
+            width = near ? 32 - __builtin_clz(near) - lo : 0;
         }
-    }
-    __syncthreads();
-    // the layer-l cells of the brick interior, compacted
-    int mine[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int q = tid + 256 * h;
-        const int x = kBrickHalo + q % kBrick, y = kBrickHalo + (q / kBrick) % kBrick,
-                  z = kBrickHalo + q / (kBrick * kBrick);
-        const int idx = (z * kBrickSpan + y) * kBrickSpan + x;
-        mine[h] = ss[idx] == kStTarget ? idx : -1;
-    }
-    int total = 0;
-    {   // by ballots: wave sums, then each cell's place within its wave
-        const unsigned long long b0 = __ballot(mine[0] >= 0), b1 = __ballot(mine[1] >= 0);
-        const unsigned long long lt = (1ull << lane) - 1ull;
-        __syncthreads();   // (s_wave was read for the anchor)
-        if (lane == 0) s_wave[wid] = __popcll(b0) + __popcll(b1);
-        __syncthreads();
-        int wb = 0;
+        // the row's place among the wave's rows: a prefix sum of the widths, bit by bit
+        int total = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int t = s_wave[i];
-            if (i < wid) wb += t;
-            total += t;
+            const unsigned long long m = __ballot((width >> i) & 1);
+            place += __popcll(m & lt) << i;
+            total += __popcll(m) << i;
         }
-        if (mine[0] >= 0) cells[wb + __popcll(b0 & lt)] = (uint16_t)mine[0];
-        if (mine[1] >= 0) cells[wb + __popcll(b0) + __popcll(b1 & lt)] = (uint16_t)mine[1];
+        if (lane == 0) B.ctl[3 + wid] = total;
+    } else {
+        // the layer's cells, listed by wave 3: a row of the brick per lane, a column at a time
+        const int y = lane / kBrick, z = lane % kBrick;
+        const unsigned mine = kHalf && z / (kBrick / 2) != half
+                                  ? 0u
+                                  : reinterpret_cast<const uint8_t*>(B.target)[lane];
+        int total = 0;
+#pragma unroll
+        for (int x = 0; x < kBrick; ++x) {
+            const unsigned long long m = __ballot((mine >> x) & 1u);
+            if ((mine >> x) & 1u)
+                B.cells[total + __popcll(m & lt)] =
+                    (uint16_t)cell_code(kBrickHalo + x, kBrickHalo + y, kBrickHalo + z);
+            total += __popcll(m);
+        }
+        if (lane == 0) {
+            B.ctl[6] = total;
+            B.ctl[7] = 0;
+        }
+    }
+    __syncthreads();
+    const int total = uniform_int(B.ctl[6]);
+    const int span0 = uniform_int(B.ctl[3]), span1 = uniform_int(B.ctl[4]);
+    const int span = span0 + span1 + uniform_int(B.ctl[5]);
+    const bool whole = kHalf || sizeof(T) == 4 || span <= span_cells<T>();
+    const bool staged = b.r_s == kBrickHalo && whole;
+    // log2 of the lanes per cell: as many as keep every cell of the brick in one pass
+    const int sh = total <= 256 / 16 ? 4 : (total <= 256 / 8 ? 3 : 2);
+    // The brick's anchor A: xi of the first cell of the region (in row order) that carries
+    // data for layer l; one exists, since every layer-l cell has a neighbour in layer l - 1.
+    // Staged values are xi - A: the fit is invariant to the shift, and the offsets are small
+    // (the region spans 12 cells), which keeps the moments accurate and lets the
+    // reduced-precision form hold them in FP32.
+    int qa = uniform_int(B.ctl[0]);
+    if (qa < 0) qa = uniform_int(B.ctl[1]);
+    if (qa < 0) qa = uniform_int(B.ctl[2]);
+    const int ca = qa < 0 ? 0 : brick_cell(cx, (unsigned)qa);
+    const double a0 = load_global(xi + ca), a1 = load_global(xi + cx.nc + ca),
+                 a2 = load_global(xi + 2 * cx.nc + ca);
+    const bool nrm = l <= b.normal_layers;
+    double g0 = 0.0, g1 = 0.0, g2 = 0.0;
+    if (nrm && staged && total > 0) {
+        const int cell = brick_cell(cx, B.cells[min(tid >> sh, total - 1)]);
+        g0 = load_global(d->normals + cell);
+        g1 = load_global(d->normals + cx.nc + cell);
+        g2 = load_global(d->normals + 2 * cx.nc + cell);
+    }
+    if (tid < S2 && staged) {
+        place += (wid > 0 ? span0 : 0) + (wid > 1 ? span1 : 0);
+        B.rows[tid] = data | (unsigned)(place - lo + 16) << 12;
+        const unsigned needed = data & near;
+        const unsigned code = cell_code(lo, ry, rz);
+        for (int j = 0; j < width; ++j)
+            B.slots[place + j] =
+                (uint16_t)((code + j) | (((needed >> (lo + j)) & 1u) ? kCellNeeded : 0u));
+    }
+    __syncthreads();
+    if (staged) {
+        // Every load of the thread is issued before its first use, so they cost one round
+        // trip; a cell that is not needed loads the anchor's (no load waits on a branch).
+        constexpr int kH = (span_cells<T>() + 255) / 256;
+        unsigned on = 0u;   // bit h: cell h of the thread is needed
+        double v0[kH], v1[kH], v2[kH];
+#pragma unroll
+        for (int h = 0; h < kH; ++h) {
+            if (256 * h < span) {   // uniform
+                const int i = tid + 256 * h;
+                const unsigned q = i < span ? B.slots[i] : 0u;
+                const bool n = (q & kCellNeeded) != 0u;
+                on |= n ? 1u << h : 0u;
+                const int c = n ? brick_cell(cx, q) : ca;
+                v0[h] = load_global(xi + c);
+                v1[h] = load_global(xi + cx.nc + c);
+                v2[h] = load_global(xi + 2 * cx.nc + c);
+            }
+        }
+        cx.A[0] = uniform_double(a0);
+        cx.A[1] = uniform_double(a1);
+        cx.A[2] = uniform_double(a2);
+#pragma unroll
+        for (int h = 0; h < kH; ++h) {
+            const int i = tid + 256 * h;
+            if (i < span) {
+                const bool n = (on >> h) & 1u;
+                B.sx[i] = n ? (T)(v0[h] - cx.A[0]) : T(0);
+                B.sx[span_cells<T>() + i] = n ? (T)(v1[h] - cx.A[1]) : T(0);
+                B.sx[2 * span_cells<T>() + i] = n ? (T)(v2[h] - cx.A[2]) : T(0);
+            }
+        }
+        __syncthreads();
+        fit_cells<T>(d, nrm, cx, total, sh, B, tables, g0, g1, g2);
+    } else if (whole) {   // every cell is gathered from global memory
+        cx.A[0] = uniform_double(a0);
+        cx.A[1] = uniform_double(a1);
+        cx.A[2] = uniform_double(a2);
+        for (int ci = tid; ci < total; ci += 256) B.cells[ci] |= (uint16_t)kCellOpen;
+        if (tid == 0) B.ctl[7] = 1;
+    }
+    __syncthreads();   // the list's flags; the rest of the LDS is free for the next brick
+    if (!whole || uniform_int(B.ctl[7])) {
+        if constexpr (kHalf) {
+            fit_open_cells<T>(b, pk, l, lds, sh, staged, cx.A[0], cx.A[1], cx.A[2]);
+        } else {
+            finish_brick<T>(b, pk, l, lds, tables, whole ? sh : 0, cx.A[0], cx.A[1], cx.A[2]);
+            if (!whole) tab = -2;
+        }
         __syncthreads();
     }
+}
 
-    // lanes per cell: as many as keep every cell of the brick in one pass of the block
-    if (total <= 256 / 16)
-        fit_cells<16, T>(b, d, st, l, ox, oy, oz, total, lds, s_rlen, s_anchor);
-    else if (total <= 256 / 8)
-        fit_cells<8, T>(b, d, st, l, ox, oy, oz, total, lds, s_rlen, s_anchor);
-    else
-        fit_cells<4, T>(b, d, st, l, ox, oy, oz, total, lds, s_rlen, s_anchor);
-    __syncthreads();   // the LDS is reused by the next brick
+// What a brick's fits left: its open cells, or (sh == 0) all of it, in two halves.
+template <typename T>
+static __device__ __noinline__ void finish_brick(FitArgs b, unsigned long long pk, int l,
+                                                 unsigned char* lds, FitTables tables, int sh,
+                                                 double A0, double A1, double A2) {
+    if (sh != 0) {
+        fit_open_cells<T>(b, pk, l, lds, sh, b.r_s == kBrickHalo, A0, A1, A2);
+        return;
+    }
+    int tab = -2;   // (the weights are filled again)
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half)
+        extrap_brick<T, true>(b, pk, l, lds, tables, tab, half);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1231,30 +1560,25 @@ __global__ __launch_bounds__(256, kSpheres ? 8 : 4) void k_normal(Batch b) {
 // the blocks of each XCD stride over a contiguous range of it, so neighbouring bricks,
 // whose halos overlap, share one L2.
 template <typename T>
-__global__ __launch_bounds__(256, 3) void k_extrap(Batch b, int l) {
+__global__ __launch_bounds__(256, 4) void k_extrap(Batch b, int l) {
     HIP_DYNAMIC_SHARED(double, lds_d)
     unsigned char* lds = reinterpret_cast<unsigned char*>(lds_d);
-    __shared__ int s_wave[4];
-    __shared__ double s_anchor[3];
     __shared__ double s_rlen[kRlen];
-    if (threadIdx.x < kRlen) s_rlen[threadIdx.x] = rlen_entry(nullptr, threadIdx.x);
-    int tab = -1;   // the loaded table: equal spacings
+    __shared__ RowSums s_rows[kRowSets];
     const unsigned long long* dl = b.dlist + (int64_t)(l - 1) * b.dlist_cap;
-    const int count = uniform_int((int)min((int64_t)b.dcount[l - 1], b.dlist_cap));
-    __syncthreads();   // s_rlen
+    const int count = (int)min((int64_t)load_const(b.dcount + l - 1), b.dlist_cap);
+    const FitTables tables = {s_rlen, s_rows};   // (read after the first brick's barriers)
+    fill_fit_tables(tables);
+    int tab = -1;   // the loaded weights: equal spacings
+    const FitArgs args = {b.solids, b.stats, b.normal_layers, b.r_s, b.r_max};
     const XcdRange rg = xcd_range(count);
     for (int e = rg.begin; e < rg.end; e += rg.stride) {
-        const unsigned long long pk = dl[e];
-        const int s = uniform_int((int)(pk >> 32));
-        const int bx = uniform_int((int)(pk & 1023ull));
-        const int by = uniform_int((int)((pk >> 10) & 1023ull));
-        const int bz = uniform_int((int)((pk >> 20) & 1023ull));
-        unsigned long long* st = b.stats + (int64_t)s * kStatWords;
-        if (st[ST_FLAGS] & FLAG_TRUNCATED) continue;   // uniform: whole block skips
-        extrap_brick<T>(b, s, st, l, bx, by, bz, lds, s_wave, s_anchor, s_rlen, tab);
+        const unsigned long long pk = load_const(dl + e);
+        const unsigned long long* st = b.stats + (int64_t)entry_solid(pk) * kStatWords;
+        if (load_const(st + ST_FLAGS) & FLAG_TRUNCATED) continue;   // uniform: the block skips
+        extrap_brick<T, false>(args, pk, l, lds, tables, tab, 0);
     }
 }
-
 
 // ------------------------------------------------------------------------------------
 // Persistent band launch: the normals and the fits of every layer of the whole batch in
@@ -1291,14 +1615,13 @@ struct BandLds {
     int* s_pref;           // [kMaxLayers * kBuckets + 1]
     int* s_wave;           // [4]
     int* s_ctl;            // [4]: ticket, wait result
-    double* s_anchor;      // [3]
-    double* s_rlen;        // [kRlen]
+    FitTables tables;      // the fits' weights [kRlen] and row sums [kRowSets]
     unsigned long long* s_acc;  // [kLT]
 };
 
 __host__ __device__ constexpr size_t band_small_bytes() {
-    return sizeof(int) * (kMaxLayers * kBuckets + 1 + 4 + 4) + sizeof(double) * (3 + kRlen) +
-           sizeof(unsigned long long) * kLT + 64;
+    return sizeof(int) * (kMaxLayers * kBuckets + 1 + 4 + 4) + sizeof(double) * kRlen +
+           sizeof(RowSums) * kRowSets + sizeof(unsigned long long) * kLT + 64;
 }
 
 __device__ __forceinline__ BandLds band_lds(unsigned char* lds, size_t work_bytes) {
@@ -1310,9 +1633,9 @@ __device__ __forceinline__ BandLds band_lds(unsigned char* lds, size_t work_byte
     L.s_list = reinterpret_cast<uint16_t*>(lds + sizeof(double) * kNCells + kNCells +
                                            kBrick * kBrick * kBrick);
     unsigned char* sm = lds + ((work_bytes + 15) & ~size_t(15));
-    L.s_anchor = reinterpret_cast<double*>(sm);
-    L.s_rlen = L.s_anchor + 3;
-    L.s_acc = reinterpret_cast<unsigned long long*>(L.s_rlen + kRlen);
+    L.tables.rlen = reinterpret_cast<double*>(sm);
+    L.tables.rows = reinterpret_cast<RowSums*>(L.tables.rlen + kRlen);
+    L.s_acc = reinterpret_cast<unsigned long long*>(L.tables.rows + kRowSets);
     L.s_pref = reinterpret_cast<int*>(L.s_acc + kLT);
     L.s_wave = L.s_pref + kMaxLayers * kBuckets + 1;
     L.s_ctl = L.s_wave + 4;
@@ -1376,8 +1699,8 @@ __global__ __launch_bounds__(256, 3) void k_band(Batch b, int work_bytes) {
     const BandLds L = band_lds(reinterpret_cast<unsigned char*>(lds_d), (size_t)work_bytes);
     BandCtl* ctl = b.band;
     const int tid = threadIdx.x;
-    if (tid < kRlen) L.s_rlen[tid] = rlen_entry(nullptr, tid);
-    int tab = -1;   // the loaded reciprocal-length table: equal spacings
+    fill_fit_tables(L.tables);
+    int tab = -1;   // the loaded weights: equal spacings
     solid_counts(b, L.s_acc);
     list_prefix(b, 1, b.Lmax, L.s_pref, L.s_wave);   // (ends with a barrier)
     const int nl = b.normal_layers;
@@ -1441,9 +1764,9 @@ __global__ __launch_bounds__(256, 3) void k_band(Batch b, int work_bytes) {
             int layer = 1;
             const unsigned long long pk = list_entry(b, 1, b.Lmax, L.s_pref, e, &layer);
             const int s = uniform_int((int)(pk >> 32));
-            const int bx = uniform_int((int)(pk & 1023ull));
-            const int by = uniform_int((int)((pk >> 10) & 1023ull));
-            const int bz = uniform_int((int)((pk >> 20) & 1023ull));
+            const unsigned place = (unsigned)uniform_int((int)pk);
+            const unsigned long long pk_uniform = ((unsigned long long)s << 32) | place;
+            const int bx = entry_x(place), by = entry_y(place), bz = entry_z(place);
             layer = uniform_int(layer);
             unsigned long long* st = b.stats + (int64_t)s * kStatWords;
             if (!(st[ST_FLAGS] & FLAG_TRUNCATED)) {   // uniform: no fit follows a truncation
@@ -1451,8 +1774,8 @@ __global__ __launch_bounds__(256, 3) void k_band(Batch b, int work_bytes) {
                     normal_brick<false>(b.solids + s, st, layer, bx, by, bz, L.s_phi, L.s_flag, L.s_lab,
                                  L.s_list, L.s_wave);
                 else
-                    extrap_brick<T>(b, s, st, p, bx, by, bz, L.work, L.s_wave, L.s_anchor,
-                                    L.s_rlen, tab);
+                    extrap_brick<T, false>({b.solids, b.stats, b.normal_layers, b.r_s, b.r_max},
+                                           pk_uniform, p, L.work, L.tables, tab, 0);
             }
         }
         ++pend;   // (a skipped item counts too)

@@ -186,7 +186,7 @@ int plan(const rmx_grid* const* grids, const rmx_solid* solids, int32_t n_solids
     // layer's list holds each brick of the boxes at most once).
     int64_t bricks = 0;
     for (const DevSolid& d : p->solids) bricks += (int64_t)d.nbx * d.nby * d.nbz;
-    const int eb = tune.extrap_blocks > 0 ? tune.extrap_blocks : 3 * std::max(cu, 1);
+    const int eb = tune.extrap_blocks > 0 ? tune.extrap_blocks : 4 * std::max(cu, 1);
     p->extrap_blocks = (int)std::max<int64_t>(std::min<int64_t>(eb, bricks), 1);
     p->dlist_cap = std::max<int64_t>(bricks, 1);
     // normal: as many blocks as are resident at once (each block scans the brick lists
