@@ -8,11 +8,16 @@
 
 namespace rmx {
 
-// Tiles of 8^3 grid cells (two per thread).  (64 x 4 x 2 tiles, whose waves write whole
-// 512-byte rows, measured no faster on cavity256 and twice as slow on the suspension: a
-// wider tile lists more candidate solids for every cell.)
+// Tiles of 8^3 grid cells.  (A wider tile lists more candidate solids for every cell.)
 constexpr int kBlurTX = 8, kBlurTY = 8, kBlurTZ = 8;
 constexpr int kBlurTileCells = kBlurTX * kBlurTY * kBlurTZ;
+
+// Units of the fill (a wave each): consecutive values of a region that spans whole planes of
+// its array, or rows along x of one plane.
+constexpr int kFillRun = 8192, kFillRows = 16;
+__host__ __device__ inline bool fill_planes(int E0, int E1, int n0, int n1) {
+    return E0 == n0 && E1 == n1;
+}
 
 // One solid: its box in the grid, phi0, and its fields (from an extrapolation call).
 struct BlurDev {
@@ -23,7 +28,8 @@ struct BlurDev {
     const int8_t* labels;                // [e2][e1][e0]
     double* phi;                         // [e2][e1][e0] or null
     double G;                            // shear modulus
-    int64_t row0;                        // first row of the solid in the fill's rows
+    int64_t unit0;                       // first unit of the solid in the fill
+    int64_t units[3];                    // its units: of its cells ([0]), or of its faces per axis
 };
 
 struct BlurBatch {
@@ -39,9 +45,9 @@ struct BlurBatch {
     const int32_t* active;       // tiles with a candidate
     int32_t* n_covered;          // tiles of `active` with a covered cell (zeroed per call)
     int32_t* covered;            // [n_active]: those tiles, in the order the scan found them
-    int64_t fill_rows;           // rows (along x) of the boxes' cells or faces, all solids
+    int64_t fill_units;          // units of the fill, all solids
     double eps;
-    double h[3];                 // spacing of each axis
+    double h[3], rh[3];          // spacing of each axis, and 1 / spacing
     double* H;                   // [n2][n1][n0] or null
     double* tau[3];              // [6][n2 + f2][n1 + f1][n0 + f0] or null, f_b = 1 if b == a
                                  // and axis a is walled, else 0

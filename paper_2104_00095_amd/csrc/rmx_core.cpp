@@ -653,25 +653,27 @@ static int blur_setup(rmx_ctx* c, const rmx_grid* grid, const rmx_solid* solids,
         d.phi = phi ? phi[m] : nullptr;
         d.G = G ? G[m] : 0.0;
     }
-    // the fill's rows along x: per solid its box's cells (H), or per axis a and component
-    // the box's faces along a (ext_a + 1 of them, at most n on a periodic axis)
-    int64_t rows = 0;
+    // the fill's units: per solid its box's cells (H), or per axis a and component the box's
+    // faces along a (ext_a + 1 of them, at most n on a periodic axis)
+    int64_t units = 0;
     for (int m = 0; m < n; ++m) {
-        sd[m].row0 = rows;
+        sd[m].unit0 = units;
         const rmx_solid& s = solids[m];
-        if (!stress) {
-            rows += (int64_t)s.ext[1] * s.ext[2];
-            continue;
-        }
-        for (int a = 0; a < 3; ++a) {
-            int64_t e[3];
+        for (int a = 0; a < (stress ? 3 : 1); ++a) {
+            int64_t e[3], g[3];
             for (int x = 0; x < 3; ++x) {
-                e[x] = s.ext[x] + (x == a ? 1 : 0);
-                if (grid->periodic[x] && e[x] > grid->n[x]) e[x] = grid->n[x];
+                const int face = stress && x == a ? 1 : 0;
+                g[x] = grid->n[x] + (grid->periodic[x] ? 0 : face);
+                e[x] = std::min<int64_t>(s.ext[x] + face, g[x]);
             }
-            rows += 6 * e[1] * e[2];
+            const int64_t per = fill_planes((int)e[0], (int)e[1], (int)g[0], (int)g[1])
+                                    ? (e[0] * e[1] * e[2] + kFillRun - 1) / kFillRun
+                                    : e[2] * ((e[1] + kFillRows - 1) / kFillRows);
+            sd[m].units[a] = (stress ? 6 : 1) * per;
+            units += sd[m].units[a];
         }
     }
+    if (units > ((int64_t)1 << 32)) return RMX_E_ARG;   // (a launch's blocks)
     auto al = [](size_t v) { return (v + 255) & ~size_t(255); };
     const size_t o_start = al(sizeof(BlurDev) * n);
     const size_t o_list = o_start + al(sizeof(int32_t) * (nt + 1));
@@ -720,6 +722,7 @@ static int blur_setup(rmx_ctx* c, const rmx_grid* grid, const rmx_solid* solids,
         b->periodic[a] = grid->periodic[a] ? 1 : 0;
         b->tiles[a] = (int32_t)T[a];
         b->h[a] = grid->spacing[a] > 0.0 ? grid->spacing[a] : grid->h;
+        b->rh[a] = 1.0 / b->h[a];
     }
     b->n_active = (int32_t)active.size();
     b->tile_start = reinterpret_cast<const int32_t*>(base + o_start);
@@ -728,7 +731,7 @@ static int blur_setup(rmx_ctx* c, const rmx_grid* grid, const rmx_solid* solids,
     b->n_covered = reinterpret_cast<int32_t*>(base + o_ncov);
     b->covered = reinterpret_cast<int32_t*>(base + o_cov);
     b->eps = eps;
-    b->fill_rows = rows;
+    b->fill_units = units;
     return RMX_OK;
 }
 

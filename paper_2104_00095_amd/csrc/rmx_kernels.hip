@@ -1015,52 +1015,6 @@ __device__ __forceinline__ void fit_cells(DevSolidC* d, bool nrm, const BrickCtx
     }
 }
 
-// The 12 labels of a staged row as bits: data (label in [0, l)) and cells of layer l.  base:
-// the box index of the row's column 0, which may lie before the box row's first cell;
-// columns outside [0, n0) give no bit.  One 16-byte load at any alignment holds the row and
-// two labels more on each side (so that the address is a multiple of 4 where n0 is); near
-// the ends of the array the window is moved inside it and the bits shifted back.
-struct RowBits {
-    unsigned data, target;
-};
-struct __attribute__((packed, aligned(1))) Labels16 {
-    uint32_t w[4];
-};
-
-// Bits 7, 15, 23, 31 of x as a nibble (the products never overlap in bits 21..24).
-__device__ __forceinline__ unsigned high_bits(unsigned x) {
-    return (((x & 0x80808080u) >> 7) * 0x00204081u >> 21) & 15u;
-}
-
-__device__ __forceinline__ RowBits label_row_bits(const int8_t* __restrict__ labels, int nc,
-                                                  int base, int ox, int n0, int l) {
-    const int lo = max(0, -ox), hi = min(kBrickSpan, n0 - ox);
-    const unsigned valid = ((1u << hi) - 1u) & ~((1u << lo) - 1u);
-    unsigned below = 0u, upto = 0u;   // labels in [0, l) and in [0, l], bit i: column i
-    if (nc >= 16) {
-        const int a = base - 2, w = min(max(a, 0), nc - 16);
-        const auto* v = (const RMX_GLOBAL_AS Labels16*)(labels + w);
-        // (b | 0x80) - l has its high bit clear only where b < l: -1 is 255, and no byte
-        // borrows from the next
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const unsigned q = v->w[u] | 0x80808080u;
-            below |= high_bits(~(q - 0x01010101u * (unsigned)l)) << (4 * u);
-            upto |= high_bits(~(q - 0x01010101u * (unsigned)(l + 1))) << (4 * u);
-        }
-        // column j lies at window place a - w + 2 + j, with -4 <= a - w <= 11
-        below = (below << 2) >> (a - w + 4);
-        upto = (upto << 2) >> (a - w + 4);
-    } else {
-        for (int j = lo; j < hi; ++j) {
-            const int lab = load_global(labels + base + j);
-            below |= (lab >= 0 && lab < l) ? 1u << j : 0u;
-            upto |= (lab >= 0 && lab <= l) ? 1u << j : 0u;
-        }
-    }
-    return {below & valid, upto & ~below & valid};
-}
-
 // A brick is bound by the latency of its dependent loads and by the instructions of its
 // fits, not by bandwidth.  It takes two round trips: the labels (one 16-byte load per row),
 // then xi of the cells that some fit reads -- the data within radius 2 of a cell of the
