@@ -145,8 +145,10 @@ __global__ __launch_bounds__(256) void k_blur_scan(BlurBatch b) {
 // its faces along an axis: ext_a + 1 of them along a, at most n on a periodic axis) is cut
 // into units, a wave each: 8192 consecutive values where the region spans whole planes of
 // the array (16-byte stores), else 16 rows along x of one plane.  Bound by the stores where
-// planes are whole: 2.6 GB of stress zeros of one 256^3 box 427 us (6.1 TB/s; a row along x
-// per wave 469 us).
+// planes are whole: 2.4 GB of stress zeros of one 256^3 box 409 us (5.9 TB/s; a row along x
+// per wave 469 us).  The runs bypass the caches (427 us otherwise: they hold nothing of use
+// to the next kernel); the rows of small boxes do not (235 against 136 us for 376 MB on 40
+// boxes: a row's ends share cache lines with cells outside the box).
 // ------------------------------------------------------------------------------------
 __device__ __forceinline__ int fill_extent(const BlurBatch& b, BlurDevC* s, int a, int ax) {
     const int e = s->ext[ax] + (ax == a ? 1 : 0);
@@ -170,11 +172,9 @@ __device__ __forceinline__ void fill_run(double* p, int64_t n, double v, int lan
         ++p;
         --n;
     }
-    struct alignas(16) Two {
-        double a, b;
-    };
+    typedef double Two __attribute__((ext_vector_type(2)));
     Two* q = reinterpret_cast<Two*>(p);
-    for (int64_t i = lane; i < n / 2; i += 64) q[i] = Two{v, v};
+    for (int64_t i = lane; i < n / 2; i += 64) __builtin_nontemporal_store(Two{v, v}, q + i);
     if ((n & 1) && lane == 0) p[n - 1] = v;
 }
 
