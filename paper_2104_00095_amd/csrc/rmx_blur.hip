@@ -237,7 +237,6 @@ __global__ __launch_bounds__(256) void k_blur_fill(BlurBatch b) {
 
 // Blocks of the full kernels: they stride over the covered tiles.
 constexpr int kBlurFullBlocks = 4096;
-constexpr int kBlurExactBlocks = 1024;   // (few tiles: what the card holds at once)
 
 // Bits of a tile's 64 rows (row r = 8 z + y per lane, `bits` its columns) as a list of cell
 // numbers x + 8 r, by one wave; returns their number.
@@ -258,8 +257,9 @@ __device__ __forceinline__ int list_cells(unsigned bits, int lane, uint16_t* lis
 // cells first, so each thread takes two cells of the tile and visits the candidates.
 // Otherwise the covered cells of a tile are listed by one wave; the certificates decide most
 // weights; the cells they leave are listed again, so that the exact distances (a bisection)
-// run in full waves.  Measured: 40 ellipsoids 95 -> 81 us (bound by the bisection's
-// instructions); 8 spheres in 256^3 16.6 -> 15.6 us (the listed form took 27 us there).
+// run in full waves.  Measured: 40 ellipsoids 95 -> 44 us (81 us with a bisection of each
+// point; bound by the chain of the distance); 8 spheres in 256^3 16.6 -> 15.6 us (the listed
+// form took 27 us there).
 __global__ __launch_bounds__(256) void k_blur_heaviside_spheres(BlurBatch b) {
     const int tid = threadIdx.x;
     const int images = b.periodic[0] || b.periodic[1] || b.periodic[2] ? 8 : 1;
@@ -406,33 +406,14 @@ __global__ __launch_bounds__(kHeavisideThreads, 4) void k_blur_heaviside(BlurBat
 constexpr int kHaloSpan = kBlurTX + 2;                            // a tile with a halo of 1
 constexpr int kHaloCells = kHaloSpan * kHaloSpan * kHaloSpan;     // 1000
 
-// Where an ellipsoid's distance is close below eps, 1 - H_eps is a small difference of two
-// numbers near 1, and the rounding of the distance shows in it as units of 1e-16.  A tile
-// with such a face where the stress is above this many shear moduli (a map folded far from
-// its solid) is computed again with every weight from phi0 itself, bit for bit; elsewhere the
-// unit stays under 2e-13 of the modulus.
-constexpr double kSteepStress = 1000.0;
-
-// The weight 1 - H_eps(phi0) of a solid at x; *near_eps: see above.
-template <bool kSpheres, bool kExact>
+// The weight 1 - H_eps(phi0) of a solid at x.
+template <bool kSpheres>
 __device__ __forceinline__ double face_weight(BlurDevC* s, double x0, double x1, double x2,
-                                              double eps, bool* near_eps) {
-    const ShapeR sh = blur_shape(s);
-    double p;
-    if (kSpheres || sh.kind == 1) {
-        p = phi0_sphere(sh, x0, x1, x2);
-    } else if (kExact) {
-        p = phi0(sh, x0, x1, x2);
-    } else {
-        double w;
-        if (weight_certain(sh, x0, x1, x2, eps, &w)) return w;
-        double y0, y1, y2;
-        body(sh, x0, x1, x2, y0, y1, y2);
-        const double dist = distance_newton(sh.e0, sh.e1, sh.e2, y0, y1, y2);
-        p = interior(sh, x0, x1, x2) ? -dist : dist;
-        *near_eps = p > 0.9 * eps && p < (1.0 + 1e-12) * eps;
-    }
-    return 1.0 - heaviside_eps(p, eps);
+                                              double eps) {
+    if constexpr (kSpheres)
+        return 1.0 - heaviside_eps(phi0_sphere(blur_shape(s), x0, x1, x2), eps);
+    else
+        return weight_at(blur_shape(s), x0, x1, x2, eps);
 }
 
 // a / b from r = 1 / b to rounding: the quotient and one residual correction (none where an
@@ -465,20 +446,20 @@ __device__ __forceinline__ unsigned face_bits(const unsigned* rows, int a, int y
 // bits, the faces whose stencil is covered listed by three waves (an axis each), xi of the
 // covered cells of the dilated tile staged in LDS once for the three axes, then the listed
 // faces in full waves.  Tiles that one solid covers (nearly all) store the stress directly;
-// where several do, they add to tau (0 from the fill) in ascending order, and the sums with
+// where several do, they add up in tau in ascending order, and the sums with
 // S > 1 are divided at the end.  Bound by instructions and by the latency of each tile's
-// chain (labels, list, xi, faces).  Measured: 40 ellipsoids in 128x128x256 420 -> 111 us,
-// 8 spheres in 256^3 159 -> 104 us (before: an 8^3 tile's faces on all threads, ten label
+// chain (labels, list, xi, faces).  Measured: 40 ellipsoids in 128x128x256 420 -> 120 us,
+// 8 spheres in 256^3 159 -> 93 us (before: an 8^3 tile's faces on all threads, ten label
 // bytes and thirty xi loads per face, the bisection of the distance in sparse waves).
-// kExact: the tiles flagged by the first form again, weights from phi0 (4 us if none).
-template <bool kSpheres, bool kExact>
-__global__ __launch_bounds__(256, 4) void k_blur_stress(BlurBatch b) {
+template <bool kSpheres>
+__global__ __launch_bounds__(256, 3) void k_blur_stress(BlurBatch b) {
     constexpr int S = kHaloSpan, S2 = kHaloSpan * kHaloSpan;
     __shared__ double s_xi[3][kHaloCells];
     __shared__ unsigned s_rows[S2];
     __shared__ uint16_t s_list[3][kBlurTileCells];
     __shared__ int s_n[3];
     __shared__ double s_sum[3][kBlurTileCells];   // S of each face, where several solids cover
+    __shared__ double s_w[3 * kBlurTileCells];    // the listed faces' weights
     const int images = b.periodic[0] || b.periodic[1] || b.periodic[2] ? 8 : 1;
     const int n_tiles = load_const(b.n_covered);
     int64_t nf[3];
@@ -491,11 +472,7 @@ __global__ __launch_bounds__(256, 4) void k_blur_stress(BlurBatch b) {
     }
     const XcdRange rg = xcd_range(n_tiles);   // neighbouring tiles share cache lines
     for (int k = rg.begin; k < rg.end; k += rg.stride) {
-        int t = uniform_int(b.covered[k]);   // (~tile: again, from phi0)
-        if (kExact) {
-            if (t >= 0) continue;   // uniform
-            t = ~t;
-        }
+        const int t = load_const(b.covered + k);
         const int e0 = load_const(b.tile_start + t), e1 = load_const(b.tile_start + t + 1);
         int o[3];
         tile_origin(b, t, o);
@@ -565,49 +542,62 @@ __global__ __launch_bounds__(256, 4) void k_blur_stress(BlurBatch b) {
                         for (int c = 0; c < 3; ++c) s_xi[c][tid + 256 * h] = v[h][c];
                 __syncthreads();
                 const int na = s_n[0], nb = s_n[1], n = na + nb + s_n[2];
+                // the weights first (each read by the thread that wrote it): with the distance
+                // and the stress in one loop the registers do not suffice
+                for (int j = tid; j < n; j += 256) {
+                    const int a = j < na ? 0 : (j < na + nb ? 1 : 2);
+                    const int q = s_list[a][j - (a > 0 ? na : 0) - (a > 1 ? nb : 0)];
+                    const int r = (((q >> 6) + 1) * S + ((q >> 3) & 7) + 1) * S + (q & 7) + 1;
+                    const int sa = a == 0 ? 1 : (a == 1 ? S : S2);
+                    s_w[j] = face_weight<kSpheres>(
+                        s, (s_xi[0][r - sa] + s_xi[0][r]) * 0.5,
+                        (s_xi[1][r - sa] + s_xi[1][r]) * 0.5,
+                        (s_xi[2][r - sa] + s_xi[2][r]) * 0.5, b.eps);
+                }
                 for (int j = tid; j < n; j += 256) {
                     const int a = j < na ? 0 : (j < na + nb ? 1 : 2);
                     const int q = s_list[a][j - (a > 0 ? na : 0) - (a > 1 ? nb : 0)];
                     const int x = q & 7, y = (q >> 3) & 7, z = q >> 6;
                     const int r = ((z + 1) * S + y + 1) * S + x + 1;
-                    // the face's axis first, then the other two in order
+                    // strides of the face's axis, then of the other two in order
                     const int sa = a == 0 ? 1 : (a == 1 ? S : S2), s1 = a == 0 ? S : 1,
                               s2 = a == 2 ? S : S2;
-                    const double h[3] = {a == 0 ? b.h[0] : (a == 1 ? b.h[1] : b.h[2]),
-                                         a == 0 ? b.h[1] : b.h[0], a == 2 ? b.h[1] : b.h[2]};
-                    const double rh[3] = {a == 0 ? b.rh[0] : (a == 1 ? b.rh[1] : b.rh[2]),
-                                          a == 0 ? b.rh[1] : b.rh[0], a == 2 ? b.rh[1] : b.rh[2]};
-                    // (the weight first: it holds the most registers)
-                    bool near_eps = false;
-                    const double w = face_weight<kSpheres, kExact>(
-                        s, (s_xi[0][r - sa] + s_xi[0][r]) * 0.5,
-                        (s_xi[1][r - sa] + s_xi[1][r]) * 0.5,
-                        (s_xi[2][r - sa] + s_xi[2][r]) * 0.5, b.eps, &near_eps);
-                    // columns of grad xi: differences across the face, and the mean of the
-                    // centred differences of its two cells along the other axes
-                    double A[3], P[3], Q[3];
+                    const double w = s_w[j];
+                    // J = grad xi: differences across the face, and the mean of the centred
+                    // differences of its two cells along the other axes
+                    double J[3][3];
+                    const double hx = a == 0 ? b.h[0] : 4.0 * b.h[0],
+                                 hy = a == 1 ? b.h[1] : 4.0 * b.h[1],
+                                 hz = a == 2 ? b.h[2] : 4.0 * b.h[2];
+                    const double rx = a == 0 ? b.rh[0] : 0.25 * b.rh[0],
+                                 ry = a == 1 ? b.rh[1] : 0.25 * b.rh[1],
+                                 rz = a == 2 ? b.rh[2] : 0.25 * b.rh[2];
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
                         const double* f = s_xi[c] + r;
-                        A[c] = quotient(f[0] - f[-sa], h[0], rh[0]);
-                        P[c] = quotient((f[s1 - sa] - f[-s1 - sa]) + (f[s1] - f[-s1]),
-                                        4.0 * h[1], 0.25 * rh[1]);
-                        Q[c] = quotient((f[s2 - sa] - f[-s2 - sa]) + (f[s2] - f[-s2]),
-                                        4.0 * h[2], 0.25 * rh[2]);
+                        const double A = f[0] - f[-sa];
+                        const double P = (f[s1 - sa] - f[-s1 - sa]) + (f[s1] - f[-s1]);
+                        const double Q = (f[s2 - sa] - f[-s2 - sa]) + (f[s2] - f[-s2]);
+                        J[c][0] = quotient(a == 0 ? A : P, hx, rx);
+                        J[c][1] = quotient(a == 0 ? P : (a == 1 ? A : Q), hy, ry);
+                        J[c][2] = quotient(a == 2 ? A : Q, hz, rz);
                     }
-                    // rows of F = (grad xi)^{-1}: cross products over the determinant
-                    double F[3][3];
-                    F[0][0] = P[1] * Q[2] - P[2] * Q[1];
-                    F[0][1] = P[2] * Q[0] - P[0] * Q[2];
-                    F[0][2] = P[0] * Q[1] - P[1] * Q[0];
-                    F[1][0] = Q[1] * A[2] - Q[2] * A[1];
-                    F[1][1] = Q[2] * A[0] - Q[0] * A[2];
-                    F[1][2] = Q[0] * A[1] - Q[1] * A[0];
-                    F[2][0] = A[1] * P[2] - A[2] * P[1];
-                    F[2][1] = A[2] * P[0] - A[0] * P[2];
-                    F[2][2] = A[0] * P[1] - A[1] * P[0];
-                    const double det = (A[0] * F[0][0] + A[1] * F[0][1]) + A[2] * F[0][2];
+                    // F = J^{-1} by cofactors
+                    const double c00 = J[1][1] * J[2][2] - J[1][2] * J[2][1];
+                    const double c01 = J[1][2] * J[2][0] - J[1][0] * J[2][2];
+                    const double c02 = J[1][0] * J[2][1] - J[1][1] * J[2][0];
+                    const double det = (J[0][0] * c00 + J[0][1] * c01) + J[0][2] * c02;
                     const double rd = 1.0 / det;
+                    double F[3][3];
+                    F[0][0] = c00;
+                    F[1][0] = c01;
+                    F[2][0] = c02;
+                    F[0][1] = J[0][2] * J[2][1] - J[0][1] * J[2][2];
+                    F[1][1] = J[0][0] * J[2][2] - J[0][2] * J[2][0];
+                    F[2][1] = J[0][1] * J[2][0] - J[0][0] * J[2][1];
+                    F[0][2] = J[0][1] * J[1][2] - J[0][2] * J[1][1];
+                    F[1][2] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
+                    F[2][2] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
 #pragma unroll
                     for (int c = 0; c < 3; ++c)
 #pragma unroll
@@ -615,23 +605,11 @@ __global__ __launch_bounds__(256, 4) void k_blur_stress(BlurBatch b) {
                     auto dot = [&](int c, int g) {
                         return (F[c][0] * F[g][0] + F[c][1] * F[g][1]) + F[c][2] * F[g][2];
                     };
-                    const double B00 = dot(0, 0), B11 = dot(1, 1), B22 = dot(2, 2);
-                    const double B01 = dot(0, 1), B02 = dot(0, 2), B12 = dot(1, 2);
-                    // to x, y, z: (face axis, first other, second other)
-                    const double xx = a == 0 ? B00 : B11, yy = a == 0 ? B11 : (a == 1 ? B00 : B22),
-                                 zz = a == 2 ? B00 : B22;
-                    const double xy = a == 2 ? B12 : B01, xz = a == 0 ? B02 : (a == 1 ? B12 : B01),
-                                 yz = a == 0 ? B12 : B02;
+                    const double xx = dot(0, 0), yy = dot(1, 1), zz = dot(2, 2);
+                    const double xy = dot(0, 1), xz = dot(0, 2), yz = dot(1, 2);
                     const double tr3 = ((xx + yy) + zz) / 3.0;
                     const double tau[6] = {G * (xx - tr3), G * (yy - tr3), G * (zz - tr3),
                                            G * xy, G * xz, G * yz};
-                    if (near_eps) {
-                        double top = 0.0;
-#pragma unroll
-                        for (int c = 0; c < 6; ++c) top = fmax(top, fabs(tau[c]));
-                        // (for the exact form; every thread that stores, stores this)
-                        if (top > kSteepStress * fabs(G)) b.covered[k] = ~t;
-                    }
                     double* out = a == 0 ? b.tau[0] : (a == 1 ? b.tau[1] : b.tau[2]);
                     const int64_t pf = a == 0 ? nf[0] : (a == 1 ? nf[1] : nf[2]);
                     const int64_t p0 = a == 0 ? f0[0] : b.grid[0], p1 = a == 1 ? f1[1] : b.grid[1];
@@ -698,14 +676,10 @@ hipError_t launch_blur_stress(const BlurBatch& b, hipStream_t st) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int g = b.n_active < kBlurFullBlocks ? b.n_active : kBlurFullBlocks;
-    if (b.spheres) {
-        hipLaunchKernelGGL((k_blur_stress<true, false>), dim3(g), dim3(256), 0, st, b);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL((k_blur_stress<false, false>), dim3(g), dim3(256), 0, st, b);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int gx = b.n_active < kBlurExactBlocks ? b.n_active : kBlurExactBlocks;
-    hipLaunchKernelGGL((k_blur_stress<false, true>), dim3(gx), dim3(256), 0, st, b);
+    if (b.spheres)
+        hipLaunchKernelGGL(k_blur_stress<true>, dim3(g), dim3(256), 0, st, b);
+    else
+        hipLaunchKernelGGL(k_blur_stress<false>, dim3(g), dim3(256), 0, st, b);
     return hipGetLastError();
 }
 

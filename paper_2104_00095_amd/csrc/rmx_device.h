@@ -19,7 +19,12 @@ __device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_read
 #define RMX_CONST_AS __attribute__((address_space(4)))
 // Product of two integers below 2^23 in magnitude (full rate; a 32-bit product is not).
 __device__ __forceinline__ int mul24(int a, int b) { return __mul24(a, b); }
+// 1/x and x^(-1/2) in single precision, as the hardware approximates them.
+__device__ __forceinline__ float rcp_fast(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ float rsq_fast(float x) { return __builtin_amdgcn_rsqf(x); }
 #else
+inline float rcp_fast(float x) { return 1.0f / x; }
+inline float rsq_fast(float x) { return 1.0f / sqrtf(x); }
 #define RMX_CONST_AS
 inline int mul24(int a, int b) { return a * b; }
 #endif
@@ -59,7 +64,8 @@ struct ShapeR {
     double r00, r01, r02, r10, r11, r12, r20, r21, r22;  // rot[b][a]
 };
 
-__device__ __forceinline__ ShapeR load_shape(const DevSolid* d) {
+template <typename Solid>
+__device__ __forceinline__ ShapeR load_shape(const Solid* d) {
     ShapeR s;
     s.kind = d->kind;
     s.c0 = d->centre[0]; s.c1 = d->centre[1]; s.c2 = d->centre[2];
@@ -306,6 +312,138 @@ __device__ inline double ellipsoid_distance(double e0, double e1, double e2, dou
     return sqrt(D);
 }
 
+// A positive double n units in the last place up.
+__device__ __forceinline__ double ulps_up(double x, int n) {
+    return __longlong_as_double(__double_as_longlong(x) + n);
+}
+
+// x within [2^-60, 2^60].
+__device__ __forceinline__ bool near_one(double x) { return x >= 0x1p-60 && x <= 0x1p60; }
+
+// a / b, correctly rounded as div_mid, from a reciprocal y of b to about 2^-30.
+__device__ __forceinline__ double div_near(double a, double b, double y) {
+    const double y2 = fma(y, fma(-b, y, 1.0), y);
+    const double q = a * y2;
+    return fma(fma(-b, q, a), y2, q);
+}
+
+// The distance of ellipsoid_distance, bit for bit, without following its bisection to the
+// end.  The computed f does not increase (see ellipsoid_bisect), so the bisection ends where
+// f goes from positive to negative: if that is between adjacent numbers, or at a single 0
+// between them, it ends there whatever its path.  f at the seven numbers around a Newton
+// estimate of the root (steps in single precision, then in double, then one on the computed f
+// itself; reciprocals refined from one number to the next) settles it for most points.  A run of zeros is entered at the first midpoint that falls on it: those points
+// follow the path, from the whole bracket, by comparisons with the run's ends alone.
+// Returns false, with nothing computed, for coordinates of 0, magnitudes far from 1, and where
+// 27 numbers on one side do not hold the change of sign.
+// Bound by the latency of the chain (a wave's points take it together): 5.3 us for a wave's
+// phi0 with nothing else on the card, maps read included, against 10 us for the bounds 2^-44
+// either side of the root and the ten evaluations on the path below.
+__device__ __forceinline__ bool ellipsoid_distance_near(double e0, double e1, double e2, double y0,
+                                                        double y1, double y2, double* dist) {
+#pragma clang fp contract(off)
+    const double u0 = fabs(y0), u1 = fabs(y1), u2 = fabs(y2);
+    // (with these every operand of the divisions below is of mid_range magnitude)
+    if (!(near_one(u0) && near_one(u1) && near_one(u2) && near_one(e0) && near_one(e1) &&
+          near_one(e2)))
+        return false;
+    const double q0 = e0 * e0, q1 = e1 * e1, q2 = e2 * e2;
+    const bool m1 = e1 < e0, m2 = e2 < (m1 ? e1 : e0);
+    const double qm = m2 ? q2 : (m1 ? q1 : q0);
+    const double d0 = q0 - qm, d1 = q1 - qm, d2 = q2 - qm;
+    const double c0 = e0 * u0, c1 = e1 * u1, c2 = e2 * u2;
+    const double s0 = m2 ? c2 : (m1 ? c1 : c0);
+    const double s1 = sqrt((c0 * c0 + c1 * c1) + c2 * c2);
+    // Newton steps on g(s) = F(s)^(-1/2) - 1 (F = f + 1) from the root of a point on the
+    // surface: g grows and is concave, so from the first step on the root is approached from
+    // below.  In units of qm first.
+    float pf = 1.0f;
+    {
+        const double iq = rcp_refined(qm);
+        const float D0 = (float)(d0 * iq), D1 = (float)(d1 * iq), D2 = (float)(d2 * iq);
+        const float C0 = (float)(c0 * iq), C1 = (float)(c1 * iq), C2 = (float)(c2 * iq);
+        const float S0 = (float)(s0 * iq);
+#pragma unroll 1
+        for (int k = 0; k < 4; ++k) {
+            const float i0 = rcp_fast(pf + D0), i1 = rcp_fast(pf + D1), i2 = rcp_fast(pf + D2);
+            const float t0 = C0 * i0, t1 = C1 * i1, t2 = C2 * i2;
+            const float a0 = t0 * t0, a1 = t1 * t1, a2 = t2 * t2;
+            const float F = (a0 + a1) + a2, G = fmaf(a0, i0, fmaf(a1, i1, a2 * i2));
+            const float r = rsq_fast(F);
+            pf = fmaxf(pf - (r - 1.0f) * rcp_fast(G * (r * r * r)), S0);
+        }
+    }
+    double p = fmax(qm * (double)pf, s0), G = 0.0;
+#pragma unroll 1
+    for (int k = 0; k < 8; ++k) {
+        const double i0 = rcp_refined(p + d0), i1 = rcp_refined(p + d1), i2 = rcp_refined(p + d2);
+        const double t0 = c0 * i0, t1 = c1 * i1, t2 = c2 * i2;
+        const double a0 = t0 * t0, a1 = t1 * t1, a2 = t2 * t2;
+        const double F = (a0 + a1) + a2;
+        G = fma(a0, i0, fma(a1, i1, a2 * i2));   // sum t_i^2 / (s + d_i)
+        double r = __builtin_amdgcn_rsq(F);
+        r = r * fma(-0.5 * F, r * r, 1.5);                              // F^(-1/2)
+        const double step = (r - 1.0) * rcp_refined(G * (r * r * r));   // g / g'
+        p = fmax(p - step, s0);
+        if (!(fabs(step) > 0x1p-18 * p)) break;
+    }
+    // one step on the computed f itself
+    const double i0 = rcp_refined(p + d0), i1 = rcp_refined(p + d1), i2 = rcp_refined(p + d2);
+    auto eval = [&](double s) {
+        const double t0 = div_near(c0, s + d0, i0), t1 = div_near(c1, s + d1, i1),
+                     t2 = div_near(c2, s + d2, i2);
+        return ((t0 * t0 + t1 * t1) + t2 * t2) - 1.0;
+    };
+    p = p + 0.5 * eval(p) * rcp_refined(G);
+    if (!(p > 0.0 && ulps_up(p, -40) > s0 && ulps_up(p, 40) < s1)) return false;
+    int pos = 0, neg = 0, lo = -3, hi = 3;   // signs of f at p + lo..hi units
+#pragma unroll
+    for (int k = -3; k <= 3; ++k) {
+        const double f = eval(ulps_up(p, k));
+        pos += f > 0.0;
+        neg += f < 0.0;
+    }
+#pragma unroll 1
+    for (int n = 0; n < 8 && (pos == 0 || neg == 0); ++n) {   // three more, where one is missing
+        const int from = pos == 0 ? lo - 3 : hi + 1;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double f = eval(ulps_up(p, from + k));
+            pos += f > 0.0;
+            neg += f < 0.0;
+        }
+        if (from < lo) lo = from; else hi = from + 2;
+    }
+    if (pos == 0 || neg == 0) return false;
+    const double a = ulps_up(p, lo - 1 + pos), b = ulps_up(p, hi + 1 - neg);   // the run's ends
+    const int zeros = hi - lo + 1 - pos - neg;
+    double sm = zeros == 0 ? 0.5 * (a + b) : ulps_up(a, 1);
+    if (zeros > 1) {
+        // 0.5 (s0 + s1) from halved ends, which are exact; a midpoint on the run stays
+        double h0 = 0.5 * s0, h1 = 0.5 * s1;
+        sm = h0 + h1;
+        int n = 0;
+#pragma unroll 1
+        do {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const double h = 0.5 * sm;
+                h0 = sm <= a ? h : h0;
+                h1 = sm >= b ? h : h1;
+                sm = h0 + h1;
+            }
+        } while ((sm <= a || sm >= b) && ++n < 256);
+        if (sm <= a || sm >= b) return false;
+    }
+    const double x0 = div_near(q0 * u0, sm + d0, i0), x1 = div_near(q1 * u1, sm + d1, i1),
+                 x2 = div_near(q2 * u2, sm + d2, i2);
+    double D = (x0 - u0) * (x0 - u0);
+    D = D + (x1 - u1) * (x1 - u1);
+    D = D + (x2 - u2) * (x2 - u2);
+    *dist = sqrt(D);
+    return true;
+}
+
 // phi0 of a sphere: the operations of phi0's sphere branch below, without the ellipsoid
 // code (whose registers a sphere-only kernel then does not hold).
 __device__ __forceinline__ double phi0_sphere(const ShapeR& s, double v0, double v1, double v2) {
@@ -326,7 +464,8 @@ __device__ inline double phi0(const ShapeR& s, double v0, double v1, double v2) 
     } else {
         double y0, y1, y2;
         body(s, v0, v1, v2, y0, y1, y2);
-        dist = ellipsoid_distance(s.e0, s.e1, s.e2, y0, y1, y2);
+        if (!ellipsoid_distance_near(s.e0, s.e1, s.e2, y0, y1, y2, &dist))
+            dist = ellipsoid_distance(s.e0, s.e1, s.e2, y0, y1, y2);
     }
     return interior(s, v0, v1, v2) ? -dist : dist;
 }

@@ -1302,8 +1302,41 @@ __device__ __forceinline__ unsigned long long list_entry(const Batch& b, int l0,
 constexpr int kNSpan = kBrick + 2;                        // brick with a halo of 1
 constexpr int kNCells = kNSpan * kNSpan * kNSpan;         // 1000
 
+// The flagged cells of the region as a list (in any order): cells tid + 256 h, by
+// ballots.  Returns their number; a block's barrier at the end.
+__device__ __forceinline__ int flagged_cells(int tid, const unsigned char* s_flag,
+                                             uint16_t* s_list, int* s_wave) {
+    const int lane = tid & 63, wid = tid >> 6;
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    unsigned long long bal[4];
+    int wsum = 0;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const int q = tid + 256 * h;
+        bal[h] = __ballot(q < kNCells && s_flag[q]);
+        wsum += __popcll(bal[h]);
+    }
+    if (lane == 0) s_wave[wid] = wsum;
+    __syncthreads();
+    int pos = 0, total = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int t = s_wave[i];
+        if (i < wid) pos += t;
+        total += t;
+    }
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const int q = tid + 256 * h;
+        if ((bal[h] >> lane) & 1ull) s_list[pos + __popcll(bal[h] & lt)] = (uint16_t)q;
+        pos += __popcll(bal[h]);
+    }
+    __syncthreads();
+    return total;
+}
+
 template <bool kSpheres>
-__device__ __forceinline__ void normal_brick(const DevSolid* d, unsigned long long* st, int l,
+__device__ __forceinline__ void normal_brick(DevSolidC* d, unsigned long long* st, int l,
                                              int bx, int by, int bz, double* s_phi,
                                              unsigned char* s_flag, int8_t* s_lab,
                                              uint16_t* s_list, int* s_wave) {
@@ -1327,6 +1360,7 @@ __device__ __forceinline__ void normal_brick(const DevSolid* d, unsigned long lo
     s_lab[tid] = inb[0] ? lv[0] : (int8_t)-1;
     s_lab[tid + 256] = inb[1] ? lv[1] : (int8_t)-1;
     __syncthreads();
+    if (load_const(st + ST_FLAGS) & FLAG_TRUNCATED) return;   // uniform: no fit follows
     // a cell of layer l needs phi0 at itself and at its six face neighbours
     for (int q = tid; q < kBrick * kBrick * kBrick; q += 256) {
         if (s_lab[q] != l) continue;
@@ -1341,37 +1375,7 @@ __device__ __forceinline__ void normal_brick(const DevSolid* d, unsigned long lo
         s_flag[r + kNSpan * kNSpan] = 1;
     }
     __syncthreads();
-    // compact the needed cells: region cell q = tid + 256 h, by ballots (the list's order
-    // does not matter)
-    int total = 0;
-    {
-        const int lane = tid & 63, wid = tid >> 6;
-        const unsigned long long lt = (1ull << lane) - 1ull;
-        unsigned long long bal[4];
-        int wsum = 0;
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            const int q = tid + 256 * h;
-            bal[h] = __ballot(q < kNCells && s_flag[q]);
-            wsum += __popcll(bal[h]);
-        }
-        if (lane == 0) s_wave[wid] = wsum;
-        __syncthreads();
-        int pos = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int t = s_wave[i];
-            if (i < wid) pos += t;
-            total += t;
-        }
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            const int q = tid + 256 * h;
-            if ((bal[h] >> lane) & 1ull) s_list[pos + __popcll(bal[h] & lt)] = (uint16_t)q;
-            pos += __popcll(bal[h]);
-        }
-        __syncthreads();
-    }
+    const int total = flagged_cells(tid, s_flag, s_list, s_wave);
     // phi0 of each needed cell once (defined: inside the box with a finite xi)
     const ShapeR sh = load_shape(d);
     const double* __restrict__ f = d->xi_normal;
@@ -1464,9 +1468,13 @@ __device__ __forceinline__ void solid_counts(const Batch& b, unsigned long long*
 }
 
 // Four waves per SIMD (at most 128 registers, none spilled): the blocks go through their
-// bricks' bisections one at a time, so resident waves hide the divide chains.  A call
-// whose solids are all spheres takes the sphere-only form (kSpheres), which holds no
-// bisection and keeps more blocks resident.
+// bricks' distances one at a time (bound by that chain: 6 of the 9 us of a brick), so resident
+// waves hide it.  The entry of a block's next brick is on its way while one is done.  40
+// ellipsoids 68 -> 36 us, one 128^3 ellipsoid 24 -> 14 us, 3 small solids 32 -> 15 us.  (Both
+// layers of a brick at once, sharing phi0: 71 against 55 us at the time, as a brick's chain
+// grows to two rounds and the blocks' shares are less even.)  A call whose solids are all
+// spheres takes the sphere-only form (kSpheres), which holds no bisection and keeps more
+// blocks resident.
 template <bool kSpheres>
 __global__ __launch_bounds__(256, kSpheres ? 8 : 4) void k_normal(Batch b) {
     __shared__ int s_wave[4];
@@ -1494,18 +1502,16 @@ __global__ __launch_bounds__(256, kSpheres ? 8 : 4) void k_normal(Batch b) {
     if (nl <= 0) return;
     const int total = s_pref[nl * kBuckets];
     const XcdRange rg = xcd_range(total);
+    int l_next = 0;   // (the next brick's entry is on its way while this one is done)
+    unsigned long long next = 0ull;
+    if (rg.begin < rg.end) next = list_entry(b, 1, nl, s_pref, rg.begin, &l_next);
     for (int e = rg.begin; e < rg.end; e += rg.stride) {
-        int l = 0;
-        const unsigned long long pk = list_entry(b, 1, nl, s_pref, e, &l);
-        const int s = uniform_int((int)(pk >> 32));
-        const int bx = uniform_int((int)(pk & 1023ull));
-        const int by = uniform_int((int)((pk >> 10) & 1023ull));
-        const int bz = uniform_int((int)((pk >> 20) & 1023ull));
-        l = uniform_int(l);
-        unsigned long long* st = b.stats + (int64_t)s * kStatWords;
-        if (st[ST_FLAGS] & FLAG_TRUNCATED) continue;   // uniform: no fit follows
-        normal_brick<kSpheres>(b.solids + s, st, l, bx, by, bz, s_phi, s_flag, s_lab, s_list,
-                               s_wave);
+        const unsigned pk = (unsigned)uniform_int((int)next);
+        const int s = uniform_int((int)(next >> 32)), l = uniform_int(l_next);
+        if (e + rg.stride < rg.end) next = list_entry(b, 1, nl, s_pref, e + rg.stride, &l_next);
+        normal_brick<kSpheres>(const_solid(b.solids, s), b.stats + (int64_t)s * kStatWords, l,
+                               entry_x(pk), entry_y(pk), entry_z(pk), s_phi, s_flag, s_lab,
+                               s_list, s_wave);
         __syncthreads();   // the LDS is reused by the next brick
     }
 }
@@ -1725,8 +1731,8 @@ __global__ __launch_bounds__(256, 3) void k_band(Batch b, int work_bytes) {
             unsigned long long* st = b.stats + (int64_t)s * kStatWords;
             if (!(st[ST_FLAGS] & FLAG_TRUNCATED)) {   // uniform: no fit follows a truncation
                 if (p == 0)
-                    normal_brick<false>(b.solids + s, st, layer, bx, by, bz, L.s_phi, L.s_flag, L.s_lab,
-                                 L.s_list, L.s_wave);
+                    normal_brick<false>(const_solid(b.solids, s), st, layer, bx, by, bz, L.s_phi,
+                                        L.s_flag, L.s_lab, L.s_list, L.s_wave);
                 else
                     extrap_brick<T, false>({b.solids, b.stats, b.normal_layers, b.r_s, b.r_max},
                                            pk_uniform, p, L.work, L.tables, tab, 0);

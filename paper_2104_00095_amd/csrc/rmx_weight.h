@@ -68,62 +68,5 @@ __device__ __forceinline__ double weight_at(const ShapeR& s, double x0, double x
     return 1.0 - heaviside_eps(phi0(s, x0, x1, x2), eps);
 }
 
-// The distance from body point y to the ellipsoid with semi-axes e by Newton's method on the
-// closest point's multiplier s, the root of F(s) = sum_i (c_i / (s + d_i))^2 = 1, to
-// rounding.  F^(-1/2) is increasing and concave in s, so its steps from the lower bound of
-// the root approach the root from below, quadratically; they run in approximate arithmetic
-// until a step is below 2^-30 of s, then two steps on F follow in full precision.  A
-// coordinate of 0 is taken as a tiny one, which moves the distance by less than its
-// rounding and keeps the root simple where the closest point leaves the coordinate plane.
-// A point that is not finite has no distance: the shortest semi-axis, outside, as phi0 has
-// for NaN.
-// (The bisection that fixes phi0 bit for bit takes about ten times the operations, in a
-// loop whose length depends on the point.)
-__device__ __forceinline__ double distance_newton(double e0, double e1, double e2, double y0,
-                                                  double y1, double y2) {
-    if (!finite3(y0, y1, y2)) return fmin(e0, fmin(e1, e2));
-    const double u0 = fmax(fabs(y0), 0x1p-180), u1 = fmax(fabs(y1), 0x1p-180),
-                 u2 = fmax(fabs(y2), 0x1p-180);
-    const double q0 = e0 * e0, q1 = e1 * e1, q2 = e2 * e2;
-    const double qm = fmin(q0, fmin(q1, q2));
-    const double d0 = q0 - qm, d1 = q1 - qm, d2 = q2 - qm;
-    const double c0 = e0 * u0, c1 = e1 * u1, c2 = e2 * u2;
-    // the root lies between a shortest axis' term alone and all terms over the shortest
-    const double s0 = d0 == 0.0 ? c0 : (d1 == 0.0 ? c1 : c2);
-    const double s1 = sqrt(fma(c0, c0, fma(c1, c1, c2 * c2)));
-    double s = s0;
-#pragma unroll 1
-    for (int k = 0; k < 100; ++k) {
-        const double i0 = rcp_refined(s + d0), i1 = rcp_refined(s + d1), i2 = rcp_refined(s + d2);
-        const double t0 = c0 * i0, t1 = c1 * i1, t2 = c2 * i2;
-        const double F = fma(t0, t0, fma(t1, t1, t2 * t2));
-        const double G = fma(t0 * t0, i0, fma(t1 * t1, i1, (t2 * t2) * i2));
-        double r = __builtin_amdgcn_rsq(F);
-        r = r * (1.5 - (0.5 * F) * (r * r));   // F^(-1/2)
-        const double step = (r - 1.0) * rcp_refined(G * (r * r * r));
-        s = fmin(fmax(s - step, s0), s1);
-        if (!(fabs(step) > 0x1p-30 * s)) break;
-    }
-    // The closest point is y_i q_i / (s + d_i), at y_i t / (s + d_i) from y with t = s - qm:
-    // t carries the distance without cancellation near the surface.
-    double t = s - qm;
-    double i0 = 0.0, i1 = 0.0, i2 = 0.0;
-#pragma unroll 1
-    for (int k = 0; k < 3; ++k) {
-        i0 = rcp_newton2(s + d0);
-        i1 = rcp_newton2(s + d1);
-        i2 = rcp_newton2(s + d2);
-        if (k == 2) break;
-        const double t0 = c0 * i0, t1 = c1 * i1, t2 = c2 * i2;
-        const double F = fma(t0, t0, fma(t1, t1, fma(t2, t2, -1.0)));
-        const double G = fma(t0 * t0, i0, fma(t1 * t1, i1, (t2 * t2) * i2));
-        const double step = 0.5 * F * rcp_refined(G);
-        s = s + step;
-        t = t + step;
-    }
-    const double v0 = u0 * i0, v1 = u1 * i1, v2 = u2 * i2;
-    return fabs(t) * sqrt(fma(v0, v0, fma(v1, v1, v2 * v2)));
-}
-
 }  // namespace dev
 }  // namespace rmx
