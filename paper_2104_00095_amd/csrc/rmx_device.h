@@ -473,7 +473,7 @@ __device__ inline double phi0(const ShapeR& s, double v0, double v1, double v2) 
 // ------------------------------------------------------------------------------------
 // Helpers.
 // ------------------------------------------------------------------------------------
-__device__ __forceinline__ int find_solid_by_chunk(const DevSolid* s, int n, int c) {
+__device__ __forceinline__ int find_solid_by_chunk(DevSolidC* s, int n, int c) {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;

@@ -45,7 +45,7 @@ using namespace dev;
 constexpr int kWaveWords = kChunkWords / 4;   // 4 segments per wave
 constexpr int kSegE = 4;                       // ellipsoid: segments per batch
 
-__device__ __forceinline__ void classify_sphere(const DevSolid* dp, const ShapeR& sh, int wb,
+__device__ __forceinline__ void classify_sphere(DevSolidC* dp, const ShapeR& sh, int wb,
                                                 int we) {
 #pragma clang fp contract(off)
     const int lane = threadIdx.x & 63;
@@ -95,8 +95,8 @@ __device__ __forceinline__ void classify_sphere(const DevSolid* dp, const ShapeR
     if (lane < kWaveWords && w0 + lane < we) mask[w0 + lane] = mw;   // one store
 }
 
-__device__ __forceinline__ void classify_ellipsoid(const DevSolid* dp, const ShapeR& sh,
-                                                   int wb, int we) {
+__device__ __forceinline__ void classify_ellipsoid(DevSolidC* dp, const ShapeR& sh, int wb,
+                                                   int we) {
     const int lane = threadIdx.x & 63;
     const int wave = uniform_int(threadIdx.x >> 6);
     const int n0 = dp->n0, W = dp->W;
@@ -104,6 +104,9 @@ __device__ __forceinline__ void classify_ellipsoid(const DevSolid* dp, const Sha
     const double* __restrict__ xi = dp->xi;
     unsigned long long* __restrict__ mask = dp->mask;
     const int first = wb + wave * kWaveWords;
+    // (semi-axes far from 1: reciprocals might leave the range)
+    const bool usual = near_one(sh.e0) && near_one(sh.e1) && near_one(sh.e2);
+    const double r0 = 1.0 / sh.e0, r1 = 1.0 / sh.e1, r2 = 1.0 / sh.e2;
 #pragma unroll 1
     for (int it = 0; it < kWaveWords; it += kSegE) {
         const int w0 = first + it;
@@ -127,13 +130,22 @@ __device__ __forceinline__ void classify_ellipsoid(const DevSolid* dp, const Sha
         }
 #pragma unroll
         for (int u = 0; u < kSegE; ++u) {
-            const unsigned long long m = __ballot(interior(sh, v0[u], v1[u], v2[u]));
+            // the form with reciprocals is within 1e-14 of the one with quotients: it decides
+            // all but the points within 1e-9 of the surface (and those that are not finite);
+            // 40 ellipsoids 22 -> 18 us, bound by the reads from there on
+            double y0, y1, y2;
+            body(sh, v0[u], v1[u], v2[u], y0, y1, y2);
+            const double q0 = y0 * r0, q1 = y1 * r1, q2 = y2 * r2;
+            const double F = (q0 * q0 + q1 * q1) + q2 * q2;
+            bool in = usual && F < 1.0 - 1e-9;
+            if (!(in || (usual && F > 1.0 + 1e-9))) in = interior(sh, v0[u], v1[u], v2[u]);
+            const unsigned long long m = __ballot(in);
             if (lane == 0 && w0 + u < we) mask[w0 + u] = m;
         }
     }
 }
 
-__device__ __forceinline__ void classify_words(const DevSolid* dp, int wb, int we) {
+__device__ __forceinline__ void classify_words(DevSolidC* dp, int wb, int we) {
     const ShapeR sh = load_shape(dp);
     if (sh.kind == 1)
         classify_sphere(dp, sh, wb, we);
@@ -151,8 +163,8 @@ __global__ __launch_bounds__(256) void k_classify(Batch b) {
         for (int i = threadIdx.x; i < nctl; i += 256) reinterpret_cast<int*>(b.band)[i] = 0;
     }
     for (int chunk = blockIdx.x; chunk < b.n_chunks; chunk += gridDim.x) {
-        const int s = uniform_int(find_solid_by_chunk(b.solids, b.n_solids, chunk));
-        const DevSolid* dp = b.solids + s;
+        const int s = find_solid_by_chunk(const_solid(b.solids, 0), b.n_solids, chunk);
+        DevSolidC* dp = const_solid(b.solids, s);
         const int nwords = dp->n1 * dp->n2 * dp->W;
         const int first = (chunk - dp->chunk_base) * kChunkWords;
         classify_words(dp, first, min(first + kChunkWords, nwords));
@@ -228,7 +240,7 @@ __device__ __forceinline__ bool brick_flag(const unsigned int* s_bmask, int l, i
 // Thread i takes aligned 4-byte slot i of the runs' slots: one word store where the slot
 // lies inside one row of its run, byte stores at a run's ends and across two rows.
 template <typename F, typename Q>
-__device__ __forceinline__ void store_tile_bytes(int8_t* dst, const DevSolid* d, int xs, int nx,
+__device__ __forceinline__ void store_tile_bytes(int8_t* dst, DevSolidC* d, int xs, int nx,
                                                  int j0, int k0, F value, Q quad) {
     const int n0 = d->n0, n1 = d->n1, n2 = d->n2;
     const int nj = min(kTileJ, n1 - j0), nk = min(kTileK, n2 - k0);
@@ -263,7 +275,7 @@ __device__ __forceinline__ void store_tile_bytes(int8_t* dst, const DevSolid* d,
 // with 16-byte aligned rows store 16-byte chunks, consecutive threads on consecutive
 // chunks of a row; other tiles go through the block's word stores.
 template <int MAXTW>
-__device__ __forceinline__ void label_tile_empty(const DevSolid* d, int wx0, int tw, int j0,
+__device__ __forceinline__ void label_tile_empty(DevSolidC* d, int wx0, int tw, int j0,
                                                  int k0) {
     const int tid = threadIdx.x;
     const int n0 = d->n0, n1 = d->n1, n2 = d->n2;
@@ -294,6 +306,31 @@ __device__ __forceinline__ void label_tile_empty(const DevSolid* d, int wx0, int
                          [](int, int) { return 0u; });
 }
 
+// i / n for 0 <= i < 4096 and n >= 1, from inv = 1.0f / n: (i + 1/2) / n is at least 1 / 2n
+// from a whole number, far above its rounding.
+__device__ __forceinline__ int quotient_by(int i, float inv) {
+    return (int)(((float)i + 0.5f) * inv);
+}
+
+// Word w of a row's words c, dilated by one cell along x.
+template <int MW>
+__device__ __forceinline__ unsigned long long x_dilated(const unsigned long long* c, int w) {
+    const unsigned long long left = w > 0 ? c[w - 1] : 0ull;
+    const unsigned long long right = w < MW - 1 ? c[w + 1] : 0ull;
+    return c[w] | (c[w] << 1) | (c[w] >> 1) | (left >> 63) | (right << 63);
+}
+
+// The OR of word idx over a row and its eight neighbour rows (stride RS, planes RS * RJ).
+__device__ __forceinline__ unsigned long long cube_rows(const unsigned long long* A, int idx,
+                                                        int RS, int RJ) {
+    unsigned long long v = 0ull;
+#pragma unroll
+    for (int dk = -1; dk <= 1; ++dk)
+#pragma unroll
+        for (int dj = -1; dj <= 1; ++dj) v |= A[idx + dj * RS + dk * RS * RJ];
+    return v;
+}
+
 template <int MAXTW>
 __global__ __launch_bounds__(kLabelThreads) void k_label(Batch b) {
     constexpr int FPL = 4 * 8 * MAXTW;   // brick flags per layer: 2 (y) x 2 (z) x 8 per word
@@ -307,8 +344,8 @@ __global__ __launch_bounds__(kLabelThreads) void k_label(Batch b) {
                                                         // [l-1][2 x 2 brick rows], bit 8w + g
 
     const int t = blockIdx.x;
-    const int s = uniform_int(b.tile_solid[t]);
-    const DevSolid* d = b.solids + s;
+    const int s = load_const(b.tile_solid + t);
+    DevSolidC* d = const_solid(b.solids, s);
     unsigned long long* st = b.stats + (int64_t)s * kStatWords;
     const int tid = threadIdx.x;
     const int n0 = d->n0, n1 = d->n1, n2 = d->n2, W = d->W, L = d->L;
@@ -336,10 +373,11 @@ __global__ __launch_bounds__(kLabelThreads) void k_label(Batch b) {
     // of each waiting for the previous one.
     unsigned long long mv[kRowsPerThread][MW];
     unsigned long long any = 0ull;
+    const float inv_rj = 1.0f / (float)RJ;
 #pragma unroll
     for (int q = 0; q < kRowsPerThread; ++q) {
         const int rr = tid + kLabelThreads * q;
-        const int rj = rr % RJ, rk = rr / RJ;
+        const int rk = quotient_by(rr, inv_rj), rj = rr - rk * RJ;
         const int jj = j0 - L + rj, kk = k0 - L + rk;
         const bool ok = rr < R && jj >= 0 && jj < n1 && kk >= 0 && kk < n2;
         const int64_t base = ok ? ((int64_t)kk * n1 + jj) * W + xr0 : 0;
@@ -362,7 +400,7 @@ __global__ __launch_bounds__(kLabelThreads) void k_label(Batch b) {
         if (rr < R) {
 #pragma unroll
             for (int w = 0; w < MW; ++w)
-                if (w < RW) A[rr * RS + w] = mv[q][w];
+                if (w < RW) A[rr * RS + w] = b.adj26 ? x_dilated<MW>(mv[q], w) : mv[q][w];
         }
     }
     __syncthreads();
@@ -378,7 +416,10 @@ __global__ __launch_bounds__(kLabelThreads) void k_label(Batch b) {
     bool trunc = false;
 #pragma unroll
     for (int w = 0; w < WPH; ++w) {
-        prev[w] = (row_ok && wb + w < tw) ? A[my + w] : 0ull;
+        prev[w] = 0ull;
+        if (row_ok && wb + w < tw)   // (the 26-neighbour form keeps dilated rows in A)
+            prev[w] = b.adj26 ? load_global(mask + ((int64_t)krow * n1 + jrow) * W + wx0 + wb + w)
+                              : A[my + w];
         p0[w] = p1[w] = p2[w] = p3[w] = p4[w] = 0ull;
         cnt0 += __popcll(prev[w]);
         // An interior cell closer than L to a box face that is no grid wall: the band
@@ -408,46 +449,51 @@ __global__ __launch_bounds__(kLabelThreads) void k_label(Batch b) {
         // One dilation step through face neighbours (or, with the 26-neighbour adjacency,
         // through every cell of the 3^3 cube), A -> B, over the rows that can still reach
         // the tile: D_l is needed only within L - l rows of it, i.e. on region rows
-        // [l, RJ - l) x [l, RK - l) (their neighbours lie inside the region).  A row's own
-        // words come from registers, its neighbour rows from LDS.
+        // [l, RJ - l) x [l, RK - l) (their neighbours lie inside the region).  The cube's
+        // dilation is the x-dilated rows' OR over 3 x 3 rows, so its form keeps the rows
+        // x-dilated: 9 LDS reads per word (25 of the plain rows took 42 us on three ragged
+        // boxes, this 37 us), and forms D_l itself for the tile's rows only.
         const unsigned long long* __restrict__ Ar = A;
         unsigned long long* __restrict__ Br = B;
-        const int SJ = RJ - 2 * l, S = SJ * (RK - 2 * l);
+        const int SJ = RJ - 2 * l, S = b.adj26 && l == L ? 0 : SJ * (RK - 2 * l);
+        const float inv_sj = 1.0f / (float)SJ;
         for (int i = tid; i < S; i += kLabelThreads) {
-            const int rk = l + i / SJ, rj = l + i % SJ;
+            const int ik = quotient_by(i, inv_sj), rk = l + ik, rj = l + i - ik * SJ;
             const int jj = j0 - L + rj, kk = k0 - L + rk;
             const bool rok = jj >= 0 && jj < n1 && kk >= 0 && kk < n2;
             const int base = (rk * RJ + rj) * RS;
             unsigned long long c[MW];
+            if (!b.adj26) {
 #pragma unroll
-            for (int w = 0; w < MW; ++w) c[w] = w < RW ? Ar[base + w] : 0ull;
+                for (int w = 0; w < MW; ++w) c[w] = w < RW ? Ar[base + w] : 0ull;
 #pragma unroll
-            for (int w = 0; w < MW; ++w) {
-                if (w >= RW) break;
-                const int idx = base + w;
-                const unsigned long long left = w > 0 ? c[w - 1] : 0ull;
-                const unsigned long long right = w < MW - 1 ? c[w + 1] : 0ull;
-                unsigned long long v = c[w] | (c[w] << 1) | (c[w] >> 1) | (left >> 63) |
-                                       (right << 63);
-                if (!b.adj26) {
-                    v |= Ar[idx - RS] | Ar[idx + RS] | Ar[idx - RS * RJ] | Ar[idx + RS * RJ];
-                } else {
-                    // cube adjacency: the x-dilated words of the eight neighbour rows
-#pragma unroll
-                    for (int dk = -1; dk <= 1; ++dk)
-#pragma unroll
-                        for (int dj = -1; dj <= 1; ++dj) {
-                            if (dj == 0 && dk == 0) continue;
-                            const int q = idx + dj * RS + dk * RS * RJ;
-                            const unsigned long long m = Ar[q];
-                            const unsigned long long ml = w > 0 ? Ar[q - 1] : 0ull;
-                            const unsigned long long mr = w + 1 < RW ? Ar[q + 1] : 0ull;
-                            v |= m | (m << 1) | (m >> 1) | (ml >> 63) | (mr << 63);
-                        }
+                for (int w = 0; w < MW; ++w) {
+                    if (w >= RW) break;
+                    const int idx = base + w;
+                    const unsigned long long v = x_dilated<MW>(c, w) | Ar[idx - RS] |
+                                                 Ar[idx + RS] | Ar[idx - RS * RJ] |
+                                                 Ar[idx + RS * RJ];
+                    const unsigned long long vm = !rok ? 0ull : (xr0 + w == W - 1 ? tail : ~0ull);
+                    Br[idx] = v & vm;
                 }
-                const unsigned long long vm = !rok ? 0ull : (xr0 + w == W - 1 ? tail : ~0ull);
-                Br[idx] = v & vm;
+            } else {
+#pragma unroll
+                for (int w = 0; w < MW; ++w) {
+                    const unsigned long long vm = !rok ? 0ull : (xr0 + w == W - 1 ? tail : ~0ull);
+                    c[w] = w < RW ? cube_rows(Ar, base + w, RS, RJ) & vm : 0ull;
+                }
+#pragma unroll
+                for (int w = 0; w < MW; ++w)
+                    if (w < RW) Br[base + w] = x_dilated<MW>(c, w);
             }
+        }
+        unsigned long long dcube[WPH];
+        if (b.adj26) {
+#pragma unroll
+            for (int w = 0; w < WPH; ++w)
+                dcube[w] = row_ok && wb + w < tw ? cube_rows(Ar, my + w, RS, RJ) &
+                                                       (wx0 + wb + w == W - 1 ? tail : ~0ull)
+                                                 : 0ull;
         }
         __syncthreads();
         unsigned long long* tmp = A;
@@ -457,7 +503,8 @@ __global__ __launch_bounds__(kLabelThreads) void k_label(Batch b) {
         unsigned int fl = 0u;   // bricks of this row holding a layer-l cell: bit 8w + g
 #pragma unroll
         for (int w = 0; w < WPH; ++w) {
-            const unsigned long long dl = (row_ok && wb + w < tw) ? A[my + w] : 0ull;
+            const unsigned long long dl =
+                b.adj26 ? dcube[w] : (row_ok && wb + w < tw ? A[my + w] : 0ull);
             const unsigned long long nw = dl & ~prev[w];
             prev[w] = dl;
             if (l & 1) p0[w] |= nw;
@@ -496,12 +543,11 @@ __global__ __launch_bounds__(kLabelThreads) void k_label(Batch b) {
 
     // Bricks holding cells of each layer, appended to the layer's list in this tile's
     // bucket: wave 0 counts every layer, reserves all layers' slots with one round of
-    // atomics, then writes the entries.  A brick lies in exactly one tile, so a tile lists
-    // at most FPL bricks per layer and its bucket never overflows.
+    // atomics, and writes the entries last, when they have returned.  A brick lies in exactly
+    // one tile, so a tile lists at most FPL bricks per layer and its bucket never overflows.
+    const int bk = t % kBuckets;
+    int mybase = 0;
     if (tid < 64) {   // (lane == tid)
-        const int bk = t % kBuckets;
-        const int64_t base0 = bucket_base(bk, b.n_tiles, b.tile_w);
-        const int64_t cap = bucket_base(bk + 1, b.n_tiles, b.tile_w) - base0;
         int mytot = 0;   // lane l - 1: bricks of layer l
         for (int l = 1; l <= L; ++l) {
             int tot = 0;
@@ -509,29 +555,7 @@ __global__ __launch_bounds__(kLabelThreads) void k_label(Batch b) {
                 tot += __popcll(__ballot(f0 + lane < FPL && brick_flag<MAXTW>(s_bmask, l, f0 + lane)));
             if (lane == l - 1) mytot = tot;
         }
-        int mybase = 0;
         if (lane < L && mytot > 0) mybase = atomicAdd(b.bcount + lane * kBuckets + bk, mytot);
-        for (int l = 1; l <= L; ++l) {
-            const int lbase = __shfl(mybase, l - 1, 64);
-            int run = 0;
-            for (int f0 = 0; f0 < FPL; f0 += 64) {
-                const int r = f0 + lane;
-                const bool f = r < FPL && brick_flag<MAXTW>(s_bmask, l, r);
-                const unsigned long long bal = __ballot(f);
-                if (f) {
-                    const int pos = lbase + run + __popcll(bal & ((1ull << lane) - 1ull));
-                    const int yz = r / (8 * MAXTW), xb = r % (8 * MAXTW);
-                    const int bx = wx0 * 8 + xb, by = 2 * tyi + (yz & 1), bz = 2 * tzi + (yz >> 1);
-                    if (pos < cap)
-                        b.blist[(int64_t)(l - 1) * b.blist_cap + base0 + pos] =
-                            ((unsigned long long)s << 32) |
-                            (unsigned long long)(bx | (by << 10) | (bz << 20));
-                    else
-                        atomicOr(st + ST_FLAGS, FLAG_OVERFLOW);
-                }
-                run += __popcll(bal);
-            }
-        }
     }
 
     // Labels: byte = layer where the cell was reached, 0xFF where not.  Each thread forms
@@ -591,6 +615,31 @@ __global__ __launch_bounds__(kLabelThreads) void k_label(Batch b) {
         if (d->decisions)
             store_tile_bytes(d->decisions, d, xs, nx, j0, k0, [](int, int) { return 0u; },
                              [](int, int) { return 0u; });
+    }
+    if (tid < 64) {
+        const int64_t base0 = bucket_base(bk, b.n_tiles, b.tile_w);
+        const int64_t cap = bucket_base(bk + 1, b.n_tiles, b.tile_w) - base0;
+        for (int l = 1; l <= L; ++l) {
+            const int lbase = __shfl(mybase, l - 1, 64);
+            int run = 0;
+            for (int f0 = 0; f0 < FPL; f0 += 64) {
+                const int r = f0 + lane;
+                const bool f = r < FPL && brick_flag<MAXTW>(s_bmask, l, r);
+                const unsigned long long bal = __ballot(f);
+                if (f) {
+                    const int pos = lbase + run + __popcll(bal & ((1ull << lane) - 1ull));
+                    const int yz = r / (8 * MAXTW), xb = r % (8 * MAXTW);
+                    const int bx = wx0 * 8 + xb, by = 2 * tyi + (yz & 1), bz = 2 * tzi + (yz >> 1);
+                    if (pos < cap)
+                        b.blist[(int64_t)(l - 1) * b.blist_cap + base0 + pos] =
+                            ((unsigned long long)s << 32) |
+                            (unsigned long long)(bx | (by << 10) | (bz << 20));
+                    else
+                        atomicOr(st + ST_FLAGS, FLAG_OVERFLOW);
+                }
+                run += __popcll(bal);
+            }
+        }
     }
 }
 
