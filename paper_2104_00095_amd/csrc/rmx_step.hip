@@ -34,6 +34,11 @@ namespace rmx {
 namespace {
 using namespace dev;
 
+typedef const RMX_CONST_AS StepDev StepDevC;
+__device__ __forceinline__ StepDevC* const_step(const StepDev* steps, int s) {
+    return (StepDevC*)(steps + s);
+}
+
 __device__ __forceinline__ double dmin2(double a, double b) { return a < b ? a : b; }
 
 // Second-order limited slope at q0 from (qm, q0, qp).
@@ -102,7 +107,7 @@ __device__ __forceinline__ double upwind_ld(double w, const double* plo, int64_t
     return 0.5 * (load_global(plo + ilo) + load_global(phi + ihi));
 }
 
-__device__ __forceinline__ int find_solid_by_word(const DevSolid* s, int n, int64_t w) {
+__device__ __forceinline__ int find_solid_by_word(DevSolidC* s, int n, int64_t w) {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -111,7 +116,7 @@ __device__ __forceinline__ int find_solid_by_word(const DevSolid* s, int n, int6
     return lo;
 }
 
-__device__ __forceinline__ int64_t axis_stride(const DevSolid* d, int a) {
+__device__ __forceinline__ int64_t axis_stride(DevSolidC* d, int a) {
     return a == 0 ? 1 : (a == 1 ? (int64_t)d->n0 : (int64_t)d->n0 * d->n1);
 }
 
@@ -125,8 +130,8 @@ struct Seg {
 
 __device__ __forceinline__ Seg segment(const StepBatch& b, int64_t w) {
     Seg g;
-    g.s = uniform_int(find_solid_by_word(b.solids, b.n_solids, w));
-    const DevSolid* d = b.solids + g.s;
+    g.s = find_solid_by_word(const_solid(b.solids, 0), b.n_solids, w);
+    DevSolidC* d = const_solid(b.solids, g.s);
     g.lw = w - d->word_base;
     const int row = (int)(g.lw / d->W);
     const int wx = (int)(g.lw - (int64_t)row * d->W);
@@ -138,7 +143,7 @@ __device__ __forceinline__ Seg segment(const StepBatch& b, int64_t w) {
 }
 
 __device__ __forceinline__ int64_t wave_segment() {
-    return (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    return (int64_t)blockIdx.x * 4 + uniform_int(threadIdx.x >> 6);
 }
 
 // ------------------------------------------------------------------------------------
@@ -167,9 +172,9 @@ __global__ __launch_bounds__(256) void k_step_scan(StepBatch b, int which) {
     // wave's 16 segments are 1 KB of consecutive labels, 16 bytes per lane, tested four at
     // a time for a byte below L + 1 (unsigned: -1 is 255).
     if (w0 < b.total_words) {
-        const int s = uniform_int(find_solid_by_word(b.solids, b.n_solids, w0));
-        const DevSolid* d = b.solids + s;
-        const int8_t* lp = which == 0 ? b.steps[s].labels_n : d->labels;
+        const int s = find_solid_by_word(const_solid(b.solids, 0), b.n_solids, w0);
+        DevSolidC* d = const_solid(b.solids, s);
+        const int8_t* lp = which == 0 ? const_step(b.steps, s)->labels_n : d->labels;
         const int64_t lw0 = w0 - d->word_base;
         const int64_t nw = (int64_t)d->W * d->n1 * d->n2;
         if (d->n0 == 64 * d->W && lw0 + kScanWords <= nw &&
@@ -201,9 +206,9 @@ __global__ __launch_bounds__(256) void k_step_scan(StepBatch b, int which) {
         const int64_t w = w0 + u;
         if (w >= b.total_words) continue;   // uniform
         if (w >= end_w) {
-            const int s = uniform_int(find_solid_by_word(b.solids, b.n_solids, w));
-            const DevSolid* d = b.solids + s;
-            lp = which == 0 ? b.steps[s].labels_n : d->labels;
+            const int s = find_solid_by_word(const_solid(b.solids, 0), b.n_solids, w);
+            DevSolidC* d = const_solid(b.solids, s);
+            lp = which == 0 ? const_step(b.steps, s)->labels_n : d->labels;
             mask = d->mask;
             n0 = d->n0;
             n1 = d->n1;
@@ -262,19 +267,23 @@ __device__ void scan_append(const StepBatch& b, int which, unsigned act, int lan
     }
 }
 
-// A listed kernel: wave i of the launch takes entries i, i + waves, ... of the
-// concatenated sub-lists.
+// A listed kernel: a wave takes one entry at a time of the concatenated sub-lists, which the
+// XCDs share in contiguous parts: a part's segments are neighbours in y and z for the most,
+// so their stencils meet in one L2.
 #define STEP_LIST_LOOP(which, body)                                                     \
     do {                                                                                \
         int pre_[kStepLists + 1];                                                       \
         pre_[0] = 0;                                                                    \
         for (int x_ = 0; x_ < kStepLists; ++x_)                                         \
-            pre_[x_ + 1] = pre_[x_] + b.counts[(which) * kStepLists + x_];               \
-        for (int i_ = (int)wave_segment(); i_ < pre_[kStepLists]; i_ += gridDim.x * 4) { \
+            pre_[x_ + 1] = pre_[x_] + load_const(b.counts + (which) * kStepLists + x_);  \
+        const XcdRange rg_ = xcd_range((pre_[kStepLists] + 3) / 4);                      \
+        for (int e_ = rg_.begin; e_ < rg_.end; e_ += rg_.stride) {                       \
+            const int i_ = e_ * 4 + uniform_int(threadIdx.x >> 6);                       \
+            if (i_ >= pre_[kStepLists]) break;                                          \
             int x_ = 0;                                                                 \
             while (i_ >= pre_[x_ + 1]) ++x_;                                            \
             const int32_t* list_ = b.lists + (int64_t)((which) * kStepLists + x_) * b.list_cap; \
-            body(b, (int64_t)list_[i_ - pre_[x_]]);                                     \
+            body(b, (int64_t)load_const(list_ + (i_ - pre_[x_])));                      \
         }                                                                               \
     } while (0)
 
@@ -284,8 +293,8 @@ __device__ void scan_append(const StepBatch& b, int which, unsigned act, int lan
 __device__ void trans_segment(const StepBatch& b, int64_t w) {
     {
         const Seg g = segment(b, w);
-        const DevSolid* d = b.solids + g.s;
-        const StepDev* sd = b.steps + g.s;
+        DevSolidC* d = const_solid(b.solids, g.s);
+        StepDevC* sd = const_step(b.steps, g.s);
         const int L = d->L;
         int lab = -1;
         if (g.i < d->n0) lab = ld(sd->labels_n, g.c);
@@ -335,7 +344,7 @@ __global__ __launch_bounds__(256) void k_step_trans(StepBatch b) {
 }
 
 // Face-normal velocity on the low face of cell (i, j, k) along axis a.
-__device__ __forceinline__ double face_vel(const StepDev* sd, const DevSolid* d, int a, int i,
+__device__ __forceinline__ double face_vel(StepDevC* sd, DevSolidC* d, int a, int i,
                                            int j, int k) {
     const int64_t n0 = d->n0, n1 = d->n1;
     if (a == 0) return ld(sd->uf[0], ((int64_t)k * n1 + j) * (n0 + 1) + i);
@@ -344,7 +353,7 @@ __device__ __forceinline__ double face_vel(const StepDev* sd, const DevSolid* d,
 }
 
 // A predicted cell: labelled 0..L-4 at step n and 3 cells inside the box.
-__device__ __forceinline__ bool predicted(const StepDev* sd, const DevSolid* d, int i, int j,
+__device__ __forceinline__ bool predicted(StepDevC* sd, DevSolidC* d, int i, int j,
                                           int k) {
     if (i < 3 || i > d->n0 - 4 || j < 3 || j > d->n1 - 4 || k < 3 || k > d->n2 - 4)
         return false;
@@ -359,8 +368,8 @@ __device__ __forceinline__ bool predicted(const StepDev* sd, const DevSolid* d, 
 // ------------------------------------------------------------------------------------
 __device__ void faces_segment(const StepBatch& b, int64_t w) {
     const Seg g = segment(b, w);
-    const DevSolid* d = b.solids + g.s;
-    const StepDev* sd = b.steps + g.s;
+    DevSolidC* d = const_solid(b.solids, g.s);
+    StepDevC* sd = const_step(b.steps, g.s);
     int lab = -1;
     if (g.i < d->n0) lab = ld(sd->labels_n, g.c);
     // a cell whose face a predicted cell reads is within L1 distance 1 of it
@@ -423,8 +432,8 @@ __device__ void predict_segment(const StepBatch& b, int64_t w) {
     const double l0 = b.lam[0], l1 = b.lam[1], l2 = b.lam[2];
     const int lane = threadIdx.x & 63;
     const Seg g = segment(b, w);
-    const DevSolid* d = b.solids + g.s;
-    const StepDev* sd = b.steps + g.s;
+    DevSolidC* d = const_solid(b.solids, g.s);
+    StepDevC* sd = const_step(b.steps, g.s);
     const int L = d->L;
     const int n0 = d->n0, n1 = d->n1, n2 = d->n2;
     const int64_t nc = d->ncell;
@@ -486,8 +495,8 @@ __global__ __launch_bounds__(256) void k_step_predict(StepBatch b) {
 __device__ void correct_segment(const StepBatch& b, int64_t w) {
     {
         const Seg g = segment(b, w);
-        const DevSolid* d = b.solids + g.s;
-        const StepDev* sd = b.steps + g.s;
+        DevSolidC* d = const_solid(b.solids, g.s);
+        StepDevC* sd = const_step(b.steps, g.s);
         const unsigned long long fl = b.stats[(int64_t)g.s * kStatWords + ST_FLAGS];
         if (fl & (FLAG_TRUNCATED | FLAG_OVERFLOW | FLAG_TIMEOUT)) return;   // uniform
         const int L = d->L;
