@@ -92,14 +92,8 @@ __device__ __forceinline__ double godunov_vel(double vd, double vu) {
     return 0.0;
 }
 
-// The left/down state if w > 0, the right/up state if w < 0, their mean if w = 0.
-__device__ __forceinline__ double upwind(double w, double lo, double hi) {
-    if (w > 0.0) return lo;
-    if (w < 0.0) return hi;
-    return 0.5 * (lo + hi);
-}
-
-// upwind() on stored states, loading only the state(s) the sign of w selects.
+// The left/down state if w > 0, the right/up state if w < 0, their mean if w = 0, from stored
+// states, loading only the one(s) that the sign of w selects.
 __device__ __forceinline__ double upwind_ld(double w, const double* plo, int64_t ilo,
                                             const double* phi, int64_t ihi) {
     if (w > 0.0) return load_global(plo + ilo);
@@ -317,24 +311,29 @@ __device__ void trans_segment(const StepBatch& b, int64_t w) {
             const double vu = vy - (0.5 + hl * vy) * v.sy;
             const double wv = godunov_vel(vd, vu);
             double* tr = sd->trans + (int64_t)t * 4 * nc;
-            tr[x] = wv;
+            // only the expansion the sign of wv selects: from x up, or from x + s down (both
+            // where it is 0).  One form for both signs, and the stores after the axis' loads
+            // (the compiler keeps them in order), so that all components' loads are in flight
+            // together (16 spheres 30 -> 28 us, 8 spheres in 256^3 52.5 -> 51).
+            const int64_t from = wv < 0.0 ? x + s : x;
+            const double coef = wv < 0.0 ? -(0.5 + hl * vy) : 0.5 - hl * vx;
+            double chosen[3];
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
-                // only the expansion the sign of wv selects (both where it is 0)
                 const double* p = sd->xi_n + q * nc;
-                double v;
-                if (wv > 0.0) {
-                    v = ld(p, x) + (0.5 - hl * vx) * slope_at(p, x, s);
-                } else if (wv < 0.0) {
-                    v = ld(p, x + s) - (0.5 + hl * vy) * slope_at(p, x + s, s);
-                } else {
-                    const Pair pq = pair_at(p, x, s);
-                    const double qd = pq.vx + (0.5 - hl * vx) * pq.sx;
-                    const double qu = pq.vy - (0.5 + hl * vy) * pq.sy;
-                    v = upwind(wv, qd, qu);
-                }
-                tr[(1 + q) * nc + x] = v;
+                chosen[q] = ld(p, from) + coef * slope_at(p, from, s);
             }
+            if (!(wv > 0.0 || wv < 0.0)) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const double* p = sd->xi_n + q * nc;
+                    chosen[q] = 0.5 * (chosen[q] + (ld(p, x + s) -
+                                                    (0.5 + hl * vy) * slope_at(p, x + s, s)));
+                }
+            }
+            tr[x] = wv;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) tr[(1 + q) * nc + x] = chosen[q];
         }
     }
 }
@@ -377,18 +376,27 @@ __device__ void faces_segment(const StepBatch& b, int64_t w) {
     if (__ballot(act) == 0ull) return;
     if (!act) return;
     const int64_t nc = d->ncell;
+    // Bound by the latency of its loads (173 MB, 2.3 TB/s on 700 000 cells with 8 waves per
+    // SIMD resident): every label and face velocity that decides is loaded before the first is
+    // used (16 spheres 37 -> 34 us, 8 spheres in 256^3 77 -> 76).  An axis' loads all ahead of
+    // its stores take 76 registers and gave up more waves than they gained (79 us).
     const bool self = predicted(sd, d, g.i, g.j, g.k);
+    bool his[3], los[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const bool next = predicted(sd, d, g.i + (a == 0), g.j + (a == 1), g.k + (a == 2));
+        const bool last = predicted(sd, d, g.i - (a == 0), g.j - (a == 1), g.k - (a == 2));
+        const double un = face_vel(sd, d, a, g.i + (a == 0), g.j + (a == 1), g.k + (a == 2));
+        const double ul = face_vel(sd, d, a, g.i, g.j, g.k);
+        his[a] = (self || next) && !(un < 0.0);
+        los[a] = (self || last) && !(ul > 0.0);
+    }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         // +a face: read by this cell or by its +a neighbour; -a face: by this cell or by its
         // -a neighbour
         // ... and only the side the face velocity's sign selects there (both where it is 0)
-        const bool hi =
-            (self || predicted(sd, d, g.i + (a == 0), g.j + (a == 1), g.k + (a == 2))) &&
-            !(face_vel(sd, d, a, g.i + (a == 0), g.j + (a == 1), g.k + (a == 2)) < 0.0);
-        const bool lo =
-            (self || predicted(sd, d, g.i - (a == 0), g.j - (a == 1), g.k - (a == 2))) &&
-            !(face_vel(sd, d, a, g.i, g.j, g.k) > 0.0);
+        const bool hi = his[a], lo = los[a];
         if (!hi && !lo) continue;
         const int t1 = a == 0 ? 1 : 0, t2 = a == 2 ? 1 : 2;
         const double hl = b.hl[a], h1 = b.hl[t1], h2 = b.hl[t2];
@@ -421,7 +429,7 @@ __device__ void faces_segment(const StepBatch& b, int64_t w) {
     }
 }
 
-__global__ __launch_bounds__(256) void k_step_faces(StepBatch b) {
+__global__ __launch_bounds__(256, 8) void k_step_faces(StepBatch b) {
     STEP_LIST_LOOP(0, faces_segment);
 }
 
