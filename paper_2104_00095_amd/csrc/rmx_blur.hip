@@ -156,12 +156,8 @@ __device__ __forceinline__ int fill_extent(const BlurBatch& b, BlurDevC* s, int 
 }
 
 __device__ __forceinline__ int find_solid_by_unit(const BlurBatch& b, int64_t u) {
-    int lo = 0, hi = b.n_solids - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (blur_solid(b, mid)->unit0 <= u) lo = mid; else hi = mid - 1;
-    }
-    return lo;
+    const BlurDev* s = b.solids;
+    return wave_search(b.n_solids, u, [s](int i) { return (int64_t)load_global(&s[i].unit0); });
 }
 
 // n values v from p on, by a wave: 16-byte stores, single ones at unaligned ends.
@@ -183,7 +179,7 @@ __global__ __launch_bounds__(256) void k_blur_fill(BlurBatch b) {
     const int lane = threadIdx.x & 63;
     const int64_t u = (int64_t)blockIdx.x * 4 + uniform_int(threadIdx.x >> 6);
     if (u >= b.fill_units) return;
-    const int m = uniform_int(find_solid_by_unit(b, u));
+    const int m = find_solid_by_unit(b, u);
     BlurDevC* s = blur_solid(b, m);
     int64_t r = u - s->unit0;
     int a = 0;

@@ -473,13 +473,26 @@ __device__ inline double phi0(const ShapeR& s, double v0, double v1, double v2) 
 // ------------------------------------------------------------------------------------
 // Helpers.
 // ------------------------------------------------------------------------------------
-__device__ __forceinline__ int find_solid_by_chunk(DevSolidC* s, int n, int c) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (s[mid].chunk_base <= c) lo = mid; else hi = mid - 1;
+// The last i in [0, n) with key(i) <= v (key ascending, key(0) <= v; v the same in every lane),
+// by a whole wave: 64 keys at a time, so that up to 64 solids take one load's latency (a
+// binary search waits for one load after the other: 0.3 to 1.4 us more per kernel, e.g. the H
+// fill of 40 solids 13.5 against 12.1 us).
+template <typename Key>
+__device__ __forceinline__ int wave_search(int n, int64_t v, Key key) {
+    const int lane = threadIdx.x & 63;
+    int base = 0, len = n;
+    while (len > 1) {   // uniform
+        const int step = (len + 63) / 64, at = lane * step;
+        bool le = false;
+        if (at < len) le = key(base + at) <= v;
+        const int skip = (__popcll(__ballot(le)) - 1) * step;
+        base += skip;
+        len = min(step, len - skip);
     }
-    return lo;
+    return uniform_int(base);
+}
+__device__ __forceinline__ int find_solid_by_chunk(const DevSolid* s, int n, int c) {
+    return wave_search(n, c, [s](int i) { return (int64_t)load_global(&s[i].chunk_base); });
 }
 
 // Exclusive scan of one int per thread over a block of NW waves.

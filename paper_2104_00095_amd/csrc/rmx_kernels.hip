@@ -163,7 +163,7 @@ __global__ __launch_bounds__(256) void k_classify(Batch b) {
         for (int i = threadIdx.x; i < nctl; i += 256) reinterpret_cast<int*>(b.band)[i] = 0;
     }
     for (int chunk = blockIdx.x; chunk < b.n_chunks; chunk += gridDim.x) {
-        const int s = find_solid_by_chunk(const_solid(b.solids, 0), b.n_solids, chunk);
+        const int s = find_solid_by_chunk(b.solids, b.n_solids, chunk);
         DevSolidC* dp = const_solid(b.solids, s);
         const int nwords = dp->n1 * dp->n2 * dp->W;
         const int first = (chunk - dp->chunk_base) * kChunkWords;

@@ -101,13 +101,8 @@ __device__ __forceinline__ double upwind_ld(double w, const double* plo, int64_t
     return 0.5 * (load_global(plo + ilo) + load_global(phi + ihi));
 }
 
-__device__ __forceinline__ int find_solid_by_word(DevSolidC* s, int n, int64_t w) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (s[mid].word_base <= w) lo = mid; else hi = mid - 1;
-    }
-    return lo;
+__device__ __forceinline__ int find_solid_by_word(const DevSolid* s, int n, int64_t w) {
+    return wave_search(n, w, [s](int i) { return (int64_t)load_global(&s[i].word_base); });
 }
 
 __device__ __forceinline__ int64_t axis_stride(DevSolidC* d, int a) {
@@ -124,7 +119,7 @@ struct Seg {
 
 __device__ __forceinline__ Seg segment(const StepBatch& b, int64_t w) {
     Seg g;
-    g.s = find_solid_by_word(const_solid(b.solids, 0), b.n_solids, w);
+    g.s = find_solid_by_word(b.solids, b.n_solids, w);
     DevSolidC* d = const_solid(b.solids, g.s);
     g.lw = w - d->word_base;
     const int row = (int)(g.lw / d->W);
@@ -166,7 +161,7 @@ __global__ __launch_bounds__(256) void k_step_scan(StepBatch b, int which) {
     // wave's 16 segments are 1 KB of consecutive labels, 16 bytes per lane, tested four at
     // a time for a byte below L + 1 (unsigned: -1 is 255).
     if (w0 < b.total_words) {
-        const int s = find_solid_by_word(const_solid(b.solids, 0), b.n_solids, w0);
+        const int s = find_solid_by_word(b.solids, b.n_solids, w0);
         DevSolidC* d = const_solid(b.solids, s);
         const int8_t* lp = which == 0 ? const_step(b.steps, s)->labels_n : d->labels;
         const int64_t lw0 = w0 - d->word_base;
@@ -186,7 +181,8 @@ __global__ __launch_bounds__(256) void k_step_scan(StepBatch b, int which) {
             return;
         }
     }
-    int lab[kScanWords];
+    int lab[kScanWords];   // as loaded: none is waited for before the last is on its way
+    int top[kScanWords];   // L of the segment's solid
     // the wave's segments are consecutive: the first one's place is computed, the rest
     // follow by steps (a new solid is located again)
     // (the solid's fields are held in registers: the mask stores could alias them)
@@ -197,10 +193,11 @@ __global__ __launch_bounds__(256) void k_step_scan(StepBatch b, int which) {
 #pragma unroll
     for (int u = 0; u < kScanWords; ++u) {
         lab[u] = -1;
+        top[u] = 0;
         const int64_t w = w0 + u;
         if (w >= b.total_words) continue;   // uniform
         if (w >= end_w) {
-            const int s = find_solid_by_word(const_solid(b.solids, 0), b.n_solids, w);
+            const int s = find_solid_by_word(b.solids, b.n_solids, w);
             DevSolidC* d = const_solid(b.solids, s);
             lp = which == 0 ? const_step(b.steps, s)->labels_n : d->labels;
             mask = d->mask;
@@ -216,10 +213,8 @@ __global__ __launch_bounds__(256) void k_step_scan(StepBatch b, int which) {
             j = row - k * n1;
         }
         const int i = wx * 64 + lane;
-        if (i < n0) {
-            const int l = ld(lp, ((int64_t)k * n1 + j) * n0 + i);
-            lab[u] = l <= L ? l : -1;
-        }
+        top[u] = L;
+        if (i < n0) lab[u] = ld(lp, ((int64_t)k * n1 + j) * n0 + i);
         if (which == 0 && lane == 0) mask[lw] = 0ull;
         ++lw;
         if (++wx == W) {
@@ -233,7 +228,7 @@ __global__ __launch_bounds__(256) void k_step_scan(StepBatch b, int which) {
 #pragma unroll
     for (int u = 0; u < kScanWords; ++u) {
         if (w0 + u >= b.total_words) break;   // uniform
-        if (__ballot(lab[u] >= 0)) act |= 1u << u;
+        if (__ballot(lab[u] >= 0 && lab[u] <= top[u])) act |= 1u << u;
     }
     scan_append(b, which, act, lane, wid, w0);
 }
