@@ -565,13 +565,13 @@ __device__ __forceinline__ RowBits label_row_bits(const int8_t* __restrict__ lab
     if (nc >= 16) {
         const int a = base - 2, w = min(max(a, 0), nc - 16);
         const auto* v = (const RMX_GLOBAL_AS Labels16*)(labels + w);
-        // (b | 0x80) - l has its high bit clear only where b < l: -1 is 255, and no byte
-        // borrows from the next
+        // (b | 0x80) - l has its high bit clear only where the low seven bits of b are below
+        // l (no byte borrows from the next); a byte with its own high bit set is negative
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const unsigned q = v->w[u] | 0x80808080u;
-            below |= high_bits(~(q - 0x01010101u * (unsigned)l)) << (4 * u);
-            upto |= high_bits(~(q - 0x01010101u * (unsigned)(l + 1))) << (4 * u);
+            const unsigned b = v->w[u], q = b | 0x80808080u;
+            below |= high_bits(~((q - 0x01010101u * (unsigned)l) | b)) << (4 * u);
+            upto |= high_bits(~((q - 0x01010101u * (unsigned)(l + 1)) | b)) << (4 * u);
         }
         // column j lies at window place a - w + 2 + j, with -14 <= a - w <= 15
         const int sh = a - w + 18;
