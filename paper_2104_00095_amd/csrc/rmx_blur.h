@@ -18,6 +18,15 @@ constexpr int kFillRun = 8192, kFillRows = 16;
 __host__ __device__ inline bool fill_planes(int E0, int E1, int n0, int n1) {
     return E0 == n0 && E1 == n1;
 }
+// Blocks of the fill (four units at a time), which stride over the units: a launch takes fewer
+// than 2^32 threads, and the units are not bounded by the arrays' sizes (a thin box has one per
+// 16 rows, and boxes may overlap).
+constexpr int kFillBlocksPerCu = 256;
+inline int fill_blocks(int64_t units, int cus) {
+    const int64_t most = (int64_t)kFillBlocksPerCu * (cus > 1 ? cus : 1);
+    const int64_t blocks = (units + 3) / 4;
+    return (int)(blocks < most ? blocks : most);
+}
 
 // One solid: its box in the grid, phi0, and its fields (from an extrapolation call).
 struct BlurDev {
@@ -46,6 +55,7 @@ struct BlurBatch {
     int32_t* n_covered;          // tiles of `active` with a covered cell (zeroed per call)
     int32_t* covered;            // [n_active]: those tiles, in the order the scan found them
     int64_t fill_units;          // units of the fill, all solids
+    int32_t fill_blocks;         // blocks that stride over them
     double eps;
     double h[3], rh[3];          // spacing of each axis, and 1 / spacing
     double* H;                   // [n2][n1][n0] or null

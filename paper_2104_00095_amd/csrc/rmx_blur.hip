@@ -175,10 +175,7 @@ __device__ __forceinline__ void fill_run(double* p, int64_t n, double v, int lan
 }
 
 template <bool STRESS>
-__global__ __launch_bounds__(256) void k_blur_fill(BlurBatch b) {
-    const int lane = threadIdx.x & 63;
-    const int64_t u = (int64_t)blockIdx.x * 4 + uniform_int(threadIdx.x >> 6);
-    if (u >= b.fill_units) return;
+__device__ __forceinline__ void fill_unit(const BlurBatch& b, int64_t u, int lane) {
     const int m = find_solid_by_unit(b, u);
     BlurDevC* s = blur_solid(b, m);
     int64_t r = u - s->unit0;
@@ -229,6 +226,13 @@ __global__ __launch_bounds__(256) void k_blur_fill(BlurBatch b) {
             }
         }
     }
+}
+
+template <bool STRESS>
+__global__ __launch_bounds__(256) void k_blur_fill(BlurBatch b) {
+    const int lane = threadIdx.x & 63;
+    int64_t u = (int64_t)blockIdx.x * 4 + uniform_int(threadIdx.x >> 6);
+    for (; u < b.fill_units; u += (int64_t)gridDim.x * 4) fill_unit<STRESS>(b, u, lane);
 }
 
 // Blocks of the full kernels: they stride over the covered tiles.
@@ -647,8 +651,7 @@ hipError_t launch_blur_heaviside(const BlurBatch& b, hipStream_t st) {
     if (b.n_active <= 0) return hipSuccess;
     hipError_t e;
     if (b.H) {
-        hipLaunchKernelGGL(k_blur_fill<false>, dim3((unsigned)((b.fill_units + 3) / 4)), dim3(256),
-                           0, st, b);
+        hipLaunchKernelGGL(k_blur_fill<false>, dim3(b.fill_blocks), dim3(256), 0, st, b);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_blur_scan<false>, dim3((b.n_active + 3) / 4), dim3(256), 0, st, b);
@@ -664,8 +667,7 @@ hipError_t launch_blur_heaviside(const BlurBatch& b, hipStream_t st) {
 
 hipError_t launch_blur_stress(const BlurBatch& b, hipStream_t st) {
     if (b.n_active <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_blur_fill<true>, dim3((unsigned)((b.fill_units + 3) / 4)), dim3(256), 0,
-                       st, b);
+    hipLaunchKernelGGL(k_blur_fill<true>, dim3(b.fill_blocks), dim3(256), 0, st, b);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_blur_scan<true>, dim3((b.n_active + 3) / 4), dim3(256), 0, st, b);

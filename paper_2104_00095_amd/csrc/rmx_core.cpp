@@ -673,7 +673,6 @@ static int blur_setup(rmx_ctx* c, const rmx_grid* grid, const rmx_solid* solids,
             units += sd[m].units[a];
         }
     }
-    if (units > ((int64_t)1 << 32)) return RMX_E_ARG;   // (a launch's blocks)
     auto al = [](size_t v) { return (v + 255) & ~size_t(255); };
     const size_t o_start = al(sizeof(BlurDev) * n);
     const size_t o_list = o_start + al(sizeof(int32_t) * (nt + 1));
@@ -732,6 +731,7 @@ static int blur_setup(rmx_ctx* c, const rmx_grid* grid, const rmx_solid* solids,
     b->covered = reinterpret_cast<int32_t*>(base + o_cov);
     b->eps = eps;
     b->fill_units = units;
+    b->fill_blocks = fill_blocks(units, c->cus);
     return RMX_OK;
 }
 
