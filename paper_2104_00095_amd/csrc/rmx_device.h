@@ -519,17 +519,30 @@ __device__ __forceinline__ void block_scan(int v, int& excl, int& total, int* s_
     __syncthreads();
 }
 
-// Entries [0, count) of a list, split into one contiguous range per XCD (workgroups are
-// dealt to the XCDs round-robin): neighbouring entries, whose halos overlap, are then
-// fetched into one L2.  The calling block takes begin, begin + stride, ... below end.
+// Entries [0, count) of a list, split into one contiguous range per XCD in proportion to its
+// blocks (workgroups are dealt to the XCDs round-robin): neighbouring entries, whose halos
+// overlap, are then fetched into one L2, and no block takes more than ceil(count / blocks)
+// entries.  (Equal ranges give some blocks of a grid that is no multiple of 8 an entry too
+// many: a lone 24^3 box, 27 blocks, 75 us per call against 60.)  The calling block takes begin,
+// begin + stride, ... below end.
 struct XcdRange {
     int begin, end, stride;
 };
 __device__ __forceinline__ XcdRange xcd_range(int count) {
     const int G = gridDim.x, b = blockIdx.x;
-    if (G < kXcds) return {b, count, G};   // (some XCD would have no block)
-    const int x = b % kXcds, per = (count + kXcds - 1) / kXcds;
-    return {x * per + b / kXcds, min(count, (x + 1) * per), (G - x + kXcds - 1) / kXcds};
+    const int x = b % kXcds;
+    if (G % kXcds == 0) {   // the XCDs have the same number of blocks (no division by G)
+        const int per = (count + kXcds - 1) / kXcds;
+        return {x * per + b / kXcds, min(count, (x + 1) * per), G / kXcds};
+    }
+    // Whole rounds of the grid, then one entry more for as many blocks as are left over, dealt
+    // over the XCDs as the blocks are.
+    const int rounds = count < G ? 0 : count / G, rest = count - rounds * G;
+    const int before = x * (G / kXcds) + min(x, G % kXcds);   // blocks of the XCDs before
+    const int mine = G / kXcds + (x < G % kXcds ? 1 : 0);
+    const int lo = rounds * before + x * (rest / kXcds) + min(x, rest % kXcds);
+    const int hi = lo + rounds * mine + rest / kXcds + (x < rest % kXcds ? 1 : 0);
+    return {lo + b / kXcds, hi, mine};
 }
 
 // The same value, through an identity lane move the compiler cannot see through: work
