@@ -1072,8 +1072,9 @@ __device__ __forceinline__ void fit_cells(DevSolidC* d, bool nrm, const BrickCtx
 // of the layer (about 650 cells; 0 where they carry no data), so that a gather reads five
 // consecutive places of a row and the block's LDS leaves room for four blocks per CU.  A
 // brick whose columns exceed the staged places (layers around solids of a few cells; not
-// in FP32, whose places hold the whole region) is staged and fitted in two halves along z
-// (kHalf, `half`), whose columns always fit.
+// in FP32, whose places hold the whole region) is staged and fitted in two halves along z,
+// whose columns always fit, by the same code: a copy of its own for the few blocks that have
+// such a brick is fetched cold (8 ellipsoids on 64 x 64 x 96: fits 52 -> 29 us).
 //
 // Of a block's 13 us on a 256^3 sphere (layers past the normal's; wall-clock stamps) the
 // gathers take 2.6 (4.2 with the normal factor), the labels' round trip 1.0, xi's 1.2, the
@@ -1084,15 +1085,12 @@ __device__ __forceinline__ void fit_cells(DevSolidC* d, bool nrm, const BrickCtx
 // gives its gathers the fewest lines (fewer lines, but 0.6 us more to transpose the bits:
 // call 144 -> 161 us), and a row's xi loaded by the thread that owns the row, without the
 // list of staged cells (three round trips instead of one: 144 -> 158 us).
+//
+// part: 0 the whole brick, 1 and 2 its halves.  Returns the part to do next, 0 for none.
 template <typename T>
-static __device__ __noinline__ void finish_brick(FitArgs b, unsigned long long pk, int l,
-                                                 unsigned char* lds, FitTables tables, int sh,
-                                                 double A0, double A1, double A2);
-
-template <typename T, bool kHalf>
-__device__ __forceinline__ void extrap_brick(const FitArgs& b, unsigned long long pk, int l,
-                                             unsigned char* lds, const FitTables& tables,
-                                             int& tab, int half) {
+__device__ __forceinline__ int extrap_brick(const FitArgs& b, unsigned long long pk, int l,
+                                            unsigned char* lds, const FitTables& tables, int& tab,
+                                            int part) {
     constexpr int S = kBrickSpan, S2 = kBrickSpan * kBrickSpan;
     const int s = entry_solid(pk);
     DevSolidC* d = const_solid(b.solids, s);
@@ -1125,7 +1123,7 @@ __device__ __forceinline__ void extrap_brick(const FitArgs& b, unsigned long lon
         const int yc = ry - kBrickHalo, zc = rz - kBrickHalo;
         if ((unsigned)yc < (unsigned)kBrick && (unsigned)zc < (unsigned)kBrick)
             reinterpret_cast<uint8_t*>(B.target)[yc * kBrick + zc] =
-                (uint8_t)(rb.target >> kBrickHalo);
+                part == 0 || zc / (kBrick / 2) == part - 1 ? (uint8_t)(rb.target >> kBrickHalo) : 0;
         // the first datum of the wave's rows
         const unsigned long long m = __ballot(data != 0u);
         if (m ? lane == __builtin_ctzll(m) : lane == 0)
@@ -1147,7 +1145,6 @@ __device__ __forceinline__ void extrap_brick(const FitArgs& b, unsigned long lon
             unsigned long long t = 0ull;
 #pragma unroll
             for (int dy = -2; dy <= 2; ++dy) t |= B.target[min(max(yc + dy, 0), kBrick - 1)];
-            if (kHalf) t &= half ? 0xFFFFFFFF00000000ull : 0x00000000FFFFFFFFull;
             t = (zs >= 0 ? t >> zs : t << -zs) & 0xFFFFFFFFFFull;   // five rows
             t |= t >> 32;
             near = (unsigned)(t | t >> 8 | t >> 16 | t >> 24) & 255u;
@@ -1168,9 +1165,7 @@ __device__ __forceinline__ void extrap_brick(const FitArgs& b, unsigned long lon
     } else {
         // the layer's cells, listed by wave 3: a row of the brick per lane, a column at a time
         const int y = lane / kBrick, z = lane % kBrick;
-        const unsigned mine = kHalf && z / (kBrick / 2) != half
-                                  ? 0u
-                                  : reinterpret_cast<const uint8_t*>(B.target)[lane];
+        const unsigned mine = reinterpret_cast<const uint8_t*>(B.target)[lane];
         int total = 0;
 #pragma unroll
         for (int x = 0; x < kBrick; ++x) {
@@ -1189,8 +1184,11 @@ __device__ __forceinline__ void extrap_brick(const FitArgs& b, unsigned long lon
     const int total = uniform_int(B.ctl[6]);
     const int span0 = uniform_int(B.ctl[3]), span1 = uniform_int(B.ctl[4]);
     const int span = span0 + span1 + uniform_int(B.ctl[5]);
-    const bool whole = kHalf || sizeof(T) == 4 || span <= span_cells<T>();
-    const bool staged = b.r_s == kBrickHalo && whole;
+    const bool staged = b.r_s == kBrickHalo;
+    if (sizeof(T) == 8 && staged && span > span_cells<T>()) {   // uniform: does not fit
+        __syncthreads();   // the LDS is free for the first half
+        return 1;
+    }
     // log2 of the lanes per cell: as many as keep every cell of the brick in one pass
     const int sh = total <= 256 / 16 ? 4 : (total <= 256 / 8 ? 3 : 2);
     // The brick's anchor A: xi of the first cell of the region (in row order) that carries
@@ -1256,7 +1254,7 @@ __device__ __forceinline__ void extrap_brick(const FitArgs& b, unsigned long lon
         }
         __syncthreads();
         fit_cells<T>(d, nrm, cx, total, sh, B, tables, g0, g1, g2);
-    } else if (whole) {   // every cell is gathered from global memory
+    } else {   // every cell is gathered from global memory
         cx.A[0] = uniform_double(a0);
         cx.A[1] = uniform_double(a1);
         cx.A[2] = uniform_double(a2);
@@ -1264,30 +1262,11 @@ __device__ __forceinline__ void extrap_brick(const FitArgs& b, unsigned long lon
         if (tid == 0) B.ctl[7] = 1;
     }
     __syncthreads();   // the list's flags; the rest of the LDS is free for the next brick
-    if (!whole || uniform_int(B.ctl[7])) {
-        if constexpr (kHalf) {
-            fit_open_cells<T>(b, pk, l, lds, sh, staged, cx.A[0], cx.A[1], cx.A[2]);
-        } else {
-            finish_brick<T>(b, pk, l, lds, tables, whole ? sh : 0, cx.A[0], cx.A[1], cx.A[2]);
-            if (!whole) tab = -2;
-        }
+    if (uniform_int(B.ctl[7])) {
+        fit_open_cells<T>(b, pk, l, lds, sh, staged, cx.A[0], cx.A[1], cx.A[2]);
         __syncthreads();
     }
-}
-
-// What a brick's fits left: its open cells, or (sh == 0) all of it, in two halves.
-template <typename T>
-static __device__ __noinline__ void finish_brick(FitArgs b, unsigned long long pk, int l,
-                                                 unsigned char* lds, FitTables tables, int sh,
-                                                 double A0, double A1, double A2) {
-    if (sh != 0) {
-        fit_open_cells<T>(b, pk, l, lds, sh, b.r_s == kBrickHalo, A0, A1, A2);
-        return;
-    }
-    int tab = -2;   // (the weights are filled again)
-#pragma unroll 1
-    for (int half = 0; half < 2; ++half)
-        extrap_brick<T, true>(b, pk, l, lds, tables, tab, half);
+    return part == 1 ? 2 : 0;
 }
 
 // ------------------------------------------------------------------------------------
@@ -1581,11 +1560,13 @@ __global__ __launch_bounds__(256, 4) void k_extrap(Batch b, int l) {
     int tab = -1;   // the loaded weights: equal spacings
     const FitArgs args = {b.solids, b.stats, b.normal_layers, b.r_s, b.r_max};
     const XcdRange rg = xcd_range(count);
-    for (int e = rg.begin; e < rg.end; e += rg.stride) {
+    int part = 0;   // (a brick that does not fit comes round again in halves)
+    for (int e = rg.begin; e < rg.end;) {
         const unsigned long long pk = load_const(dl + e);
         const unsigned long long* st = b.stats + (int64_t)entry_solid(pk) * kStatWords;
-        if (load_const(st + ST_FLAGS) & FLAG_TRUNCATED) continue;   // uniform: the block skips
-        extrap_brick<T, false>(args, pk, l, lds, tables, tab, 0);
+        if (!(load_const(st + ST_FLAGS) & FLAG_TRUNCATED))   // uniform: the block skips
+            part = extrap_brick<T>(args, pk, l, lds, tables, tab, part);
+        if (part == 0) e += rg.stride;
     }
 }
 
@@ -1783,8 +1764,11 @@ __global__ __launch_bounds__(256, 3) void k_band(Batch b, int work_bytes) {
                     normal_brick<false>(const_solid(b.solids, s), st, layer, bx, by, bz, L.s_phi,
                                         L.s_flag, L.s_lab, L.s_list, L.s_wave);
                 else
-                    extrap_brick<T, false>({b.solids, b.stats, b.normal_layers, b.r_s, b.r_max},
-                                           pk_uniform, p, L.work, L.tables, tab, 0);
+                    for (int part = 0;;) {
+                        part = extrap_brick<T>({b.solids, b.stats, b.normal_layers, b.r_s, b.r_max},
+                                               pk_uniform, p, L.work, L.tables, tab, part);
+                        if (part == 0) break;
+                    }
             }
         }
         ++pend;   // (a skipped item counts too)
