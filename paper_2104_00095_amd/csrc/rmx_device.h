@@ -52,6 +52,16 @@ __device__ __forceinline__ double uniform_double(double v) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// The same for a word and a pointer.
+__device__ __forceinline__ unsigned long long uniform_word(unsigned long long v) {
+    const unsigned lo = (unsigned)uniform_int((int)v), hi = (unsigned)uniform_int((int)(v >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
+template <typename T>
+__device__ __forceinline__ T* uniform_ptr(T* p) {
+    return reinterpret_cast<T*>(uniform_word(reinterpret_cast<unsigned long long>(p)));
+}
+
 // ------------------------------------------------------------------------------------
 // phi0 and the interior predicate.  Evaluated without contraction, in the fixed order the
 // interface documents, so that the interior decision and the normal's sign test are
@@ -798,68 +808,86 @@ struct CellCtx {
 };
 
 // Accumulate, from global memory, the moments of the eligible data within Chebyshev
-// radius r (used for radii beyond the staged halo).  The (2r+1)^2 rows (dy, dz) of the box
-// are dealt to the nl lanes of the cell.  Eq. (weight): w = 2^-(|dx|+|dy|+|dz|), times
-// the cosine between x_e - x_d = -(dx rho_x, dy rho_y, dz rho_z) h and the normal when
-// use_normal; data with (dx gx + dy gy) + dz gz >= 0 (that exact expression, no
-// contraction) get weight 0.
+// radius r <= 4 (radii beyond the staged halo, and r_s other than it).  The (2r+1)^2 rows
+// (dy, dz) of the box are dealt to the nl lanes of the cell.  Eq. (weight):
+// w = 2^-(|dx|+|dy|+|dz|), times the cosine between x_e - x_d =
+// -(dx rho_x, dy rho_y, dz rho_z) h and the normal when use_normal; data with
+// (dx gx + dy gy) + dz gz >= 0 (that exact expression, no contraction) get weight 0.
+// Bound by the latency of its loads and, for the few waves that come here, of its instructions:
+// a row's labels are one 16-byte load turned into bits, only its data are visited, and the next
+// one's xi is on its way while one is added (in one copy of the code).
 template <typename T>
 __device__ __forceinline__ void gather_any(const CellCtx& cx, int r, bool use_normal, int lq,
                                            int nl, Moments<T>& acc) {
     const int D = 2 * r + 1;
+#pragma unroll 1
     for (int row = lq; row < D * D; row += nl) {
-        const int dy = row % D - r, dz = row / D - r;
+        const int dz = row / D - r, dy = row - (dz + r) * D - r;
         const int jj = cx.j + dy, kk = cx.k + dz;
         if ((unsigned)jj >= (unsigned)cx.n1 || (unsigned)kk >= (unsigned)cx.n2) continue;
-        const int32_t rb = (kk * cx.n1 + jj) * cx.n0;
-        for (int dx = -r; dx <= r; ++dx) {
-            const int ii = cx.i + dx;
-            if ((unsigned)ii >= (unsigned)cx.n0) continue;
-            const int32_t c = rb + ii;
-            const int lab = cx.labels[c];
-            if (lab < 0 || lab >= cx.le) continue;
-            double ww = ldexp(1.0, -(abs(dx) + abs(dy) + abs(dz)));
+        const int first = (kk * cx.n1 + jj) * cx.n0 + cx.i - r;   // the box index of dx = -r
+        unsigned data = label_row_bits(cx.labels, (int)cx.ncell, first, cx.i - r, cx.n0,
+                                       cx.le).data & ((1u << D) - 1u);
+        if (data == 0u) continue;
+        const int dyz2 = dy * dy + dz * dz, ayz = abs(dy) + abs(dz);
+        int dx = __builtin_ctz(data) - r;
+        const double* p = cx.xi + (first + r);
+        double x0 = load_global(p + dx), x1 = load_global(p + cx.ncell + dx),
+               x2 = load_global(p + 2 * cx.ncell + dx), rl = c_rlen[dx * dx + dyz2];
+#pragma unroll 1
+        for (;;) {
+            data &= data - 1u;
+            const int nx = data ? __builtin_ctz(data) - r : dx;
+            const double n0 = load_global(p + nx), n1 = load_global(p + cx.ncell + nx),
+                         n2 = load_global(p + 2 * cx.ncell + nx), nrl = c_rlen[nx * nx + dyz2];
+            const double fx = (double)dx, fy = (double)dy, fz = (double)dz;
+            double ww = ldexp(1.0, -(abs(dx) + ayz));
+            bool on = true;
             if (use_normal) {
 #pragma clang fp contract(off)
-                const double fx = (double)dx, fy = (double)dy, fz = (double)dz;
                 const double dot = (fx * cx.g0 + fy * cx.g1) + fz * cx.g2;
-                if (!(dot < 0.0)) continue;
-                const double rl = cx.rho ? rlen_scaled(cx.rho, fx, fy, fz)
-                                         : c_rlen[dx * dx + dy * dy + dz * dz];
+                on = dot < 0.0;
+                if (cx.rho) rl = 1.0 / norm3(fx * cx.rho[0], fy * cx.rho[1], fz * cx.rho[2]);
                 ww = (-dot * rl * cx.rgn) * ww;
             }
-            const T tw = (T)ww;
-            const T fx = (T)dx, fy = (T)dy, fz = (T)dz;
-            const T v0 = (T)(cx.xi[c] - cx.a0), v1 = (T)(cx.xi[cx.ncell + c] - cx.a1),
-                    v2 = (T)(cx.xi[2 * cx.ncell + c] - cx.a2);
-            const T wx = tw * fx, wy = tw * fy, wz = tw * fz;
-            acc.m[0] += tw;
-            acc.m[1] += wx;
-            acc.m[2] += wy;
-            acc.m[3] += wz;
-            acc.m[4] += wx * fx;
-            acc.m[5] += wx * fy;
-            acc.m[6] += wx * fz;
-            acc.m[7] += wy * fy;
-            acc.m[8] += wy * fz;
-            acc.m[9] += wz * fz;
-            acc.r[0] += tw * v0;
-            acc.r[1] += tw * v1;
-            acc.r[2] += tw * v2;
-            acc.r[3] += wx * v0;
-            acc.r[4] += wx * v1;
-            acc.r[5] += wx * v2;
-            acc.r[6] += wy * v0;
-            acc.r[7] += wy * v1;
-            acc.r[8] += wy * v2;
-            acc.r[9] += wz * v0;
-            acc.r[10] += wz * v1;
-            acc.r[11] += wz * v2;
-            acc.g[0] += 1 + ((dx * dx) << 16);
-            acc.g[1] += dx + ((dx * dy) << 16);
-            acc.g[2] += dy + ((dx * dz) << 16);
-            acc.g[3] += dz + ((dy * dy) << 16);
-            acc.g[4] += (dy * dz) + ((dz * dz) << 16);
+            if (on) {
+                const T tw = (T)ww, tx = (T)fx, ty = (T)fy, tz = (T)fz;
+                const T v0 = (T)(x0 - cx.a0), v1 = (T)(x1 - cx.a1), v2 = (T)(x2 - cx.a2);
+                const T wx = tw * tx, wy = tw * ty, wz = tw * tz;
+                acc.m[0] += tw;
+                acc.m[1] += wx;
+                acc.m[2] += wy;
+                acc.m[3] += wz;
+                acc.m[4] += wx * tx;
+                acc.m[5] += wx * ty;
+                acc.m[6] += wx * tz;
+                acc.m[7] += wy * ty;
+                acc.m[8] += wy * tz;
+                acc.m[9] += wz * tz;
+                acc.r[0] += tw * v0;
+                acc.r[1] += tw * v1;
+                acc.r[2] += tw * v2;
+                acc.r[3] += wx * v0;
+                acc.r[4] += wx * v1;
+                acc.r[5] += wx * v2;
+                acc.r[6] += wy * v0;
+                acc.r[7] += wy * v1;
+                acc.r[8] += wy * v2;
+                acc.r[9] += wz * v0;
+                acc.r[10] += wz * v1;
+                acc.r[11] += wz * v2;
+                acc.g[0] += 1 + ((dx * dx) << 16);
+                acc.g[1] += dx + ((dx * dy) << 16);
+                acc.g[2] += dy + ((dx * dz) << 16);
+                acc.g[3] += dz + ((dy * dy) << 16);
+                acc.g[4] += (dy * dz) + ((dz * dz) << 16);
+            }
+            if (!data) break;
+            dx = nx;
+            x0 = n0;
+            x1 = n1;
+            x2 = n2;
+            rl = nrl;
         }
     }
 }

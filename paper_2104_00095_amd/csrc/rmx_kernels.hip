@@ -745,7 +745,12 @@ __device__ __forceinline__ int line_row(int i, int row) {
     return row + i + (kBrickSpan - 5) * ((i * 13) >> 6) - 2 * kBrickSpan - 2;
 }
 
-// Sums over a cell's data of radius r_s = 2, plain weights w = 2^-(|dx|+|dy|+|dz|).  A lane
+// The columns of line (dy, dz) within radius r (1 or 2), as a 5-bit set.
+__device__ __forceinline__ unsigned line_columns(int r, int dy, int dz) {
+    return r == kBrickHalo ? 31u : (abs(dy) < 2 && abs(dz) < 2 ? 14u : 0u);
+}
+
+// Sums over a cell's data of radius r = 2 (or 1), plain weights w = 2^-(|dx|+|dy|+|dz|).  A lane
 // takes every nl-th line of the box around the cell at column x of staged row `row`.  The
 // staged values are xi - A for the brick's anchor A, 0 where the cell carries no data, so a
 // line's sums over dx need no selection, and the normal matrix depends only on which of its
@@ -755,12 +760,13 @@ template <typename T>
 __device__ __forceinline__ void gather_plain(const T* __restrict__ sx,
                                              const unsigned* __restrict__ rows,
                                              const RowSums* __restrict__ row_sums, int x,
-                                             int row, int lq, int nl, Moments<T>& acc) {
+                                             int row, int r, int lq, int nl, Moments<T>& acc) {
+    const T we = r == kBrickHalo ? T(0.25) : T(0);   // the weight of dx = -2 and 2
     unsigned info = rows[line_row(lq, row)];
 #pragma unroll 1
     for (int i = lq; i < 25; i += nl) {
         const int dz = line_dz(i), dy = line_dy(i, dz);
-        const unsigned bits = (info >> (x - 2)) & 31u;
+        const unsigned bits = (info >> (x - 2)) & line_columns(r, dy, dz);
         const T* p = sx + (row_place(info) + x - 2);
         info = rows[line_row(min(i + nl, 24), row)];   // the next line's, read ahead
         if (bits == 0u) continue;   // no data: the line adds zeros
@@ -771,8 +777,8 @@ __device__ __forceinline__ void gather_plain(const T* __restrict__ sx,
         for (int c = 0; c < 3; ++c) {
             const T* v = p + c * span_cells<T>();
             const T a0 = v[0], a1 = v[1], a2 = v[2], a3 = v[3], a4 = v[4];
-            const T t0 = fma(T(0.25), a4, fma(T(0.5), a3, a2 + fma(T(0.5), a1, T(0.25) * a0)));
-            const T t1 = fma(T(0.5), a4, fma(T(0.5), a3, fma(T(-0.5), a1, T(-0.5) * a0)));
+            const T t0 = fma(we, a4, fma(T(0.5), a3, a2 + fma(T(0.5), a1, we * a0)));
+            const T t1 = fma(T(2) * we, a4, fma(T(0.5), a3, fma(T(-0.5), a1, T(-2) * we * a0)));
             acc.r[c] = fma(w, t0, acc.r[c]);
             acc.r[3 + c] = fma(w, t1, acc.r[3 + c]);
             acc.r[6 + c] = fma(wy, t0, acc.r[6 + c]);
@@ -814,13 +820,13 @@ template <typename T>
 __device__ __forceinline__ void gather_normal(const T* __restrict__ sx,
                                               const unsigned* __restrict__ rows,
                                               const double* __restrict__ rlen, int x, int row,
-                                              double g0, double g1, double g2, double rgn,
+                                              double g0, double g1, double g2, double rgn, int r,
                                               int lq, int nl, Moments<T>& acc) {
     unsigned info = rows[line_row(lq, row)];
 #pragma unroll 1
     for (int i = lq; i < 25; i += nl) {
         const int dz = line_dz(i), dy = line_dy(i, dz);
-        const unsigned bits = (info >> (x - 2)) & 31u;
+        const unsigned bits = (info >> (x - 2)) & line_columns(r, dy, dz);
         const T* p = sx + (row_place(info) + x - 2);
         info = rows[line_row(min(i + nl, 24), row)];   // the next line's, read ahead
         if (bits == 0u) continue;   // no data: the line adds zeros
@@ -881,6 +887,29 @@ __device__ __forceinline__ void gather_normal(const T* __restrict__ sx,
     }
 }
 
+// The exact rank of a staged cell's data: the integer Gram matrix of their offsets (with the
+// normal, of those of positive weight, decided as in gather_normal).
+__device__ __forceinline__ bool staged_full_rank(const unsigned* rows, int x, int row, int r,
+                                                 bool has_normal, double g0, double g1,
+                                                 double g2, int lq, int sh) {
+    int g[5] = {0, 0, 0, 0, 0};
+#pragma unroll 1
+    for (int i = lq; i < 25; i += 1 << sh) {
+        const int dz = line_dz(i), dy = line_dy(i, dz);
+        unsigned set = (rows[line_row(i, row)] >> (x - 2)) & line_columns(r, dy, dz);
+        if (has_normal) {
+#pragma clang fp contract(off)
+            const double ry = (double)dy * g1, rz = (double)dz * g2;
+#pragma unroll
+            for (int u = 0; u < 5; ++u)
+                if (!(((double)(u - 2) * g0 + ry) + rz < 0.0)) set &= ~(1u << u);
+        }
+        add_offsets(g, set, dy, dz);
+    }
+    reduce_values<5>(g, sh);
+    return det_gram(g) > 0;
+}
+
 // What the fits need of the call.
 struct FitArgs {
     const DevSolid* solids;
@@ -904,19 +933,27 @@ __device__ __forceinline__ int brick_cell(const BrickCtx& c, unsigned q) {
     return c.origin + code_z(q) * c.n01 + code_y(q) * c.n0 + code_x(q);
 }
 
-// The open cells of a brick's list: radii r_s..r_max with eq. (weight), then F1 (normal
-// factor dropped) at r_max, then F2 (kernel-weighted mean) at r_max, gathered from global
-// memory, each radius accepted by the exact rank test.  A cell fitted from the staged data
-// (`staged`) keeps that value where its r_s data turn out to have full rank.  Rare (nearly
-// degenerate cells, cells whose radius grows, or r_s other than the staged radius), and out
-// of line after the other cells, so that its registers are not the fits'.
+// The open cells of a brick's list.  Where they were fitted from the staged data (`staged`),
+// the exact rank test on the staged rows comes first: a cell whose data have full rank keeps
+// its value.  The others take the radii from there to r_max with eq. (weight), then F1 (normal factor
+// dropped) at r_max, then F2 (kernel-weighted mean) at r_max, gathered from global memory, each
+// radius accepted by the exact rank test.  Out of line after the other cells, so that its
+// registers are not the fits'; the arguments, which a call passes in vector registers, are made
+// uniform again (the descriptor's fields are then scalar loads).  8192 cells of a plate that go
+// through every radius and both fallbacks: 297 -> 66 us, 180 of them atomics of a cell each.
 template <typename T>
-static __device__ __noinline__ void fit_open_cells(FitArgs b, unsigned long long pk, int l,
-                                                   unsigned char* lds, int sh, bool staged,
-                                                   double A0, double A1, double A2) {
+static __device__ __noinline__ void fit_open_cells(FitArgs args, unsigned long long pk_, int l_,
+                                                   unsigned char* lds, int sh_, bool staged_,
+                                                   double A0_, double A1_, double A2_) {
+    const FitArgs b = {uniform_ptr(args.solids), uniform_ptr(args.stats),
+                       uniform_int(args.normal_layers), uniform_int(args.r_s),
+                       uniform_int(args.r_max)};
+    const unsigned long long pk = uniform_word(pk_);
+    const int l = uniform_int(l_), sh = uniform_int(sh_);
+    const bool staged = uniform_int(staged_);
     const BrickLds<T> B = brick_lds<T>(lds);
     const uint16_t* cells = B.cells;
-    const int total = B.ctl[6], r_s = b.r_s, r_max = b.r_max;
+    const int total = uniform_int(B.ctl[6]);
     const bool nrm = l <= b.normal_layers;
     DevSolidC* d = const_solid(b.solids, entry_solid(pk));
     unsigned long long* st = b.stats + (int64_t)entry_solid(pk) * kStatWords;
@@ -924,85 +961,118 @@ static __device__ __noinline__ void fit_open_cells(FitArgs b, unsigned long long
               oz = kBrick * entry_z(pk) - kBrickHalo;
     const int lq = threadIdx.x & ((1 << sh) - 1);
     const int64_t nc = d->ncell;
+    CellCtx cx;
+    cx.n0 = d->n0;
+    cx.n1 = d->n1;
+    cx.n2 = d->n2;
+    cx.le = l;
+    cx.ncell = nc;
+    cx.xi = d->xi;
+    cx.labels = d->labels;
+    cx.a0 = uniform_double(A0_);
+    cx.a1 = uniform_double(A1_);
+    cx.a2 = uniform_double(A2_);
+    cx.rho = d->aniso ? (const double*)d->rho : nullptr;
+    int tally = 0;   // grown, F1 and F2 cells, ten bits each (an atomic per cell takes 12 ns)
     for (int ci = threadIdx.x >> sh; ci < total; ci += 256 >> sh) {
         const unsigned q = cells[ci];
-        if (!(q & kCellOpen)) continue;   // (the same in every lane of the cell)
-        CellCtx cx;
+        if (!(q & kCellOpen)) {   // (the same in every lane of the cell)
+            tally += lq == 0 && kBrickHalo > b.r_s;   // fitted at the staged radius
+            continue;
+        }
         cx.i = ox + code_x(q);
         cx.j = oy + code_y(q);
         cx.k = oz + code_z(q);
-        cx.n0 = d->n0;
-        cx.n1 = d->n1;
-        cx.n2 = d->n2;
-        cx.le = l;
-        cx.ncell = nc;
-        cx.xi = d->xi;
-        cx.labels = d->labels;
-        cx.a0 = A0;
-        cx.a1 = A1;
-        cx.a2 = A2;
-        const int32_t cell = (cx.k * d->n1 + cx.j) * d->n0 + cx.i;
+        const int32_t cell = (cx.k * cx.n1 + cx.j) * cx.n0 + cx.i;
         cx.g0 = nrm ? load_global(d->normals + cell) : 0.0;
         cx.g1 = nrm ? load_global(d->normals + nc + cell) : 0.0;
         cx.g2 = nrm ? load_global(d->normals + 2 * nc + cell) : 0.0;
         const bool has_normal = cx.g0 != 0.0 || cx.g1 != 0.0 || cx.g2 != 0.0;
-        cx.rho = d->aniso ? (const double*)d->rho : nullptr;
+        const int dec = nrm && !has_normal ? kDecNoNormal : 0;
+        if (staged &&
+            staged_full_rank(B.rows, code_x(q), code_z(q) * kBrickSpan + code_y(q), kBrickHalo,
+                             has_normal, cx.g0, cx.g1, cx.g2, lq, sh)) {
+            if (lq == 0 && d->decisions) d->decisions[cell] = (int8_t)(kBrickHalo + dec);
+            tally += lq == 0 && kBrickHalo > b.r_s;
+            continue;
+        }
         cx.rgn = !has_normal ? 0.0
                  : d->aniso  ? rlen_scaled((const double*)d->irho, cx.g0, cx.g1, cx.g2)
                              : 1.0 / norm3(cx.g0, cx.g1, cx.g2);
         int code = -1;
-        double res[3] = {0.0, 0.0, 0.0};
-        for (int r = r_s; code < 0; ++r) {   // r_max + 1: F1, r_max + 2: F2
-            const bool f1 = r == r_max + 1, f2 = r > r_max + 1;
+        double res = 0.0;
+        const int comp = min(lq & 3, 2);   // lanes 0..2 of the cell solve and store one each
+        for (int r = staged ? kBrickHalo + 1 : b.r_s; code < 0; ++r) {   // r_max + 1: F1, + 2: F2
+            const bool f1 = r == b.r_max + 1, f2 = r > b.r_max + 1;
             if (f1 && !has_normal) continue;
             Moments<T> acc;
             zero(acc);
-            gather_any<T>(cx, min(r, r_max), has_normal && r <= r_max, lq, 1 << sh, acc);
+            gather_any<T>(cx, min(r, b.r_max), has_normal && r <= b.r_max, lq, 1 << sh, acc);
             reduce_lanes(acc, sh);
-            if (f2) {
-                const double sw = (double)acc.m[0];
+            double R[4];
 #pragma unroll
-                for (int c = 0; c < 3; ++c) res[c] = (double)acc.r[c] / sw;
+            for (int p = 0; p < 4; ++p)
+                R[p] = (double)(comp == 0 ? acc.r[3 * p]
+                                          : comp == 1 ? acc.r[3 * p + 1] : acc.r[3 * p + 2]);
+            if (f2) {
+                res = R[0] / (double)acc.m[0];
                 code = kDecF2;
             } else if (det_gram(acc.g) > 0) {
                 double M[10];
 #pragma unroll
                 for (int p = 0; p < 10; ++p) M[p] = (double)acc.m[p];
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    res[c] = solve_intercept<T>(M, (double)acc.r[c], (double)acc.r[3 + c],
-                                                (double)acc.r[6 + c], (double)acc.r[9 + c])
-                                 .value;
+                res = solve_intercept<T>(M, R[0], R[1], R[2], R[3]).value;
                 code = f1 ? kDecF1 : r;
             }
         }
+        if (lq < 3)
+            d->xi[comp * nc + cell] = (comp == 0 ? cx.a0 : (comp == 1 ? cx.a1 : cx.a2)) + res;
         if (lq == 0) {
-            if (!(staged && code == r_s)) {
-                d->xi[cell] = A0 + res[0];
-                d->xi[nc + cell] = A1 + res[1];
-                d->xi[2 * nc + cell] = A2 + res[2];
-            }
-            if (d->decisions)
-                d->decisions[cell] = (int8_t)(code + (nrm && !has_normal ? kDecNoNormal : 0));
-            if (code == kDecF1) atomicAdd(st + ST_F1, 1ull);
-            if (code == kDecF2) atomicAdd(st + ST_F2, 1ull);
-            if (code > r_s) atomicAdd(st + ST_GROWN, 1ull);   // (the F codes are larger)
+            if (d->decisions) d->decisions[cell] = (int8_t)(code + dec);
+            tally += (code > b.r_s) + ((code == kDecF1) << 10) + ((code == kDecF2) << 20);
         }
+    }
+    // (the F codes are larger than any radius; a brick has at most 512 cells)
+    tally = wave_sum(tally);
+    if ((threadIdx.x & 63) == 0 && tally) {
+        atomicAdd(st + ST_GROWN, (unsigned long long)(tally & 1023));
+        if ((tally >> 10) & 1023) atomicAdd(st + ST_F1, (unsigned long long)((tally >> 10) & 1023));
+        if (tally >> 20) atomicAdd(st + ST_F2, (unsigned long long)(tally >> 20));
     }
 }
 
-// The fits of the listed layer-l cells of a staged brick at the staged radius, 2^sh lanes
-// per cell; a cell whose data may not have full rank is left open (flagged in the list, and
+// The open cells of the list moved to its front, as a list of their own, by one wave.
+template <typename T>
+static __device__ __noinline__ void keep_open_cells(unsigned char* lds) {
+    const BrickLds<T> B = brick_lds<T>(lds);
+    const int total = uniform_int(B.ctl[6]), lane = threadIdx.x & 63;
+    int n = 0;
+    if (threadIdx.x < 64) {
+        for (int i = 0; i < total; i += 64) {
+            const unsigned q = i + lane < total ? B.cells[i + lane] : 0u;
+            const unsigned long long m = __ballot((q & kCellOpen) != 0u);
+            if (q & kCellOpen)   // (no place is written before it is read)
+                B.cells[n + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(q & ~kCellOpen);
+            n += __popcll(m);
+        }
+    }
+    __syncthreads();   // (the others have read ctl[6])
+    if (threadIdx.x == 0) B.ctl[6] = n;
+    __syncthreads();
+}
+
+// The fits of the listed layer-l cells of a staged brick at radius r, 2^sh lanes per cell; a cell whose data may not have full rank is left open (flagged in the list, and
 // ctl[7] set).  Values are relative to the brick's anchor A: xi_e = A + the fitted intercept.
 // (fn0, fn1, fn2): the normal of the group's first cell, loaded while the brick was staged.
 //
 // The rank is certain where the elimination's pivots are: the plain weights' matrix is exact,
 // and so is, to rounding, the FP64 matrix with the normal factor.  The FP32 one is not, so
 // it carries the exact integer Gram matrix of the offsets beside it.
-template <typename T>
+template <typename T, bool kAny>
 __device__ __forceinline__ void fit_cells(DevSolidC* d, bool nrm, const BrickCtx& cx, int total,
-                                          int sh, const BrickLds<T>& B, const FitTables& tab,
-                                          double fn0, double fn1, double fn2) {
+                                          int sh, int r, const BrickLds<T>& B,
+                                          const FitTables& tab, double fn0, double fn1,
+                                          double fn2) {
     double* xi = d->xi;
     int8_t* decisions = d->decisions;
     const double* normals = d->normals;
@@ -1028,13 +1098,13 @@ __device__ __forceinline__ void fit_cells(DevSolidC* d, bool nrm, const BrickCtx
             if (sizeof(T) == 4)
                 rgn = d->aniso ? rlen_scaled((const double*)d->irho, g0, g1, g2)
                                : 1.0 / norm3(g0, g1, g2);
-            gather_normal<T>(B.sx, B.rows, tab.rlen, x, row, g0, g1, g2, rgn, lq, nl, acc);
+            gather_normal<T>(B.sx, B.rows, tab.rlen, x, row, g0, g1, g2, rgn, r, lq, nl, acc);
             if (sizeof(T) == 4) {
                 reduce_values<5>(acc.g, sh);
                 full = det_gram(acc.g) > 0;
             }
         } else {
-            gather_plain<T>(B.sx, B.rows, tab.rows, x, row, lq, nl, acc);
+            gather_plain<T>(B.sx, B.rows, tab.rows, x, row, r, lq, nl, acc);
         }
         reduce_values<10>(acc.m, sh);
         reduce_values<12>(acc.r, sh);
@@ -1051,11 +1121,13 @@ __device__ __forceinline__ void fit_cells(DevSolidC* d, bool nrm, const BrickCtx
         if (lq < 3)
             xi[comp * cx.nc + cell] = (comp == 0 ? cx.A[0] : (comp == 1 ? cx.A[1] : cx.A[2])) +
                                       f.value;
+        if (!(sizeof(T) == 4 && has_normal)) full = f.certain;
+        if (kAny && r < kBrickHalo && !full)   // (the same in every lane of the cell)
+            full = staged_full_rank(B.rows, x, row, r, has_normal, g0, g1, g2, lq, sh);
         if (lq == 0) {
-            if (sizeof(T) == 4 && has_normal ? full : f.certain) {
+            if (full) {
                 if (decisions)
-                    decisions[cell] =
-                        (int8_t)(kBrickHalo + (nrm && !has_normal ? kDecNoNormal : 0));
+                    decisions[cell] = (int8_t)(r + (nrm && !has_normal ? kDecNoNormal : 0));
             } else {
                 B.cells[ci] = (uint16_t)(q | kCellOpen);
                 B.ctl[7] = 1;
@@ -1087,7 +1159,11 @@ __device__ __forceinline__ void fit_cells(DevSolidC* d, bool nrm, const BrickCtx
 // list of staged cells (three round trips instead of one: 144 -> 158 us).
 //
 // part: 0 the whole brick, 1 and 2 its halves.  Returns the part to do next, 0 for none.
-template <typename T>
+// kAny: for any r_s (else r_s is the staged radius, 2, and the kernel holds no other code).  A
+// smaller r_s is fitted from the staged data first; with a larger one every cell is gathered from
+// global memory.  Call of 40 ellipsoids with r_s = 1, a third of whose cells grow to 2: 238 us
+// (588 with both radii from global memory), with r_s = 3: 547 us (880 before gather_any's rows).
+template <typename T, bool kAny>
 __device__ __forceinline__ int extrap_brick(const FitArgs& b, unsigned long long pk, int l,
                                             unsigned char* lds, const FitTables& tables, int& tab,
                                             int part) {
@@ -1181,16 +1257,16 @@ __device__ __forceinline__ int extrap_brick(const FitArgs& b, unsigned long long
         }
     }
     __syncthreads();
-    const int total = uniform_int(B.ctl[6]);
+    int total = uniform_int(B.ctl[6]);
     const int span0 = uniform_int(B.ctl[3]), span1 = uniform_int(B.ctl[4]);
     const int span = span0 + span1 + uniform_int(B.ctl[5]);
-    const bool staged = b.r_s == kBrickHalo;
+    const bool staged = !kAny || b.r_s == kBrickHalo || (b.r_s < kBrickHalo && b.r_max >= kBrickHalo);
     if (sizeof(T) == 8 && staged && span > span_cells<T>()) {   // uniform: does not fit
         __syncthreads();   // the LDS is free for the first half
         return 1;
     }
     // log2 of the lanes per cell: as many as keep every cell of the brick in one pass
-    const int sh = total <= 256 / 16 ? 4 : (total <= 256 / 8 ? 3 : 2);
+    int sh = total <= 256 / 16 ? 4 : (total <= 256 / 8 ? 3 : 2);
     // The brick's anchor A: xi of the first cell of the region (in row order) that carries
     // data for layer l; one exists, since every layer-l cell has a neighbour in layer l - 1.
     // Staged values are xi - A: the fit is invariant to the shift, and the offsets are small
@@ -1253,8 +1329,21 @@ __device__ __forceinline__ int extrap_brick(const FitArgs& b, unsigned long long
             }
         }
         __syncthreads();
-        fit_cells<T>(d, nrm, cx, total, sh, B, tables, g0, g1, g2);
-    } else {   // every cell is gathered from global memory
+        if (kAny && b.r_s < kBrickHalo) {   // radius 1 first: the cells it settles leave the list
+            fit_cells<T, true>(d, nrm, cx, total, sh, 1, B, tables, g0, g1, g2);
+            __syncthreads();
+            keep_open_cells<T>(lds);
+            total = uniform_int(B.ctl[6]);
+            sh = total <= 256 / 16 ? 4 : (total <= 256 / 8 ? 3 : 2);
+            if (nrm && total > 0) {
+                const int cell = brick_cell(cx, B.cells[min(tid >> sh, total - 1)]);
+                g0 = load_global(d->normals + cell);
+                g1 = load_global(d->normals + cx.nc + cell);
+                g2 = load_global(d->normals + 2 * cx.nc + cell);
+            }
+        }
+        fit_cells<T, false>(d, nrm, cx, total, sh, kBrickHalo, B, tables, g0, g1, g2);
+    } else {   // (only kAny) every cell is gathered from global memory
         cx.A[0] = uniform_double(a0);
         cx.A[1] = uniform_double(a1);
         cx.A[2] = uniform_double(a2);
@@ -1547,7 +1636,7 @@ __global__ __launch_bounds__(256, kSpheres ? 8 : 4) void k_normal(Batch b) {
 // One launch per layer over the layer's dense brick list (built by the normal kernel):
 // the blocks of each XCD stride over a contiguous range of it, so neighbouring bricks,
 // whose halos overlap, share one L2.
-template <typename T>
+template <typename T, bool kAny>
 __global__ __launch_bounds__(256, 4) void k_extrap(Batch b, int l) {
     HIP_DYNAMIC_SHARED(double, lds_d)
     unsigned char* lds = reinterpret_cast<unsigned char*>(lds_d);
@@ -1565,7 +1654,7 @@ __global__ __launch_bounds__(256, 4) void k_extrap(Batch b, int l) {
         const unsigned long long pk = load_const(dl + e);
         const unsigned long long* st = b.stats + (int64_t)entry_solid(pk) * kStatWords;
         if (!(load_const(st + ST_FLAGS) & FLAG_TRUNCATED))   // uniform: the block skips
-            part = extrap_brick<T>(args, pk, l, lds, tables, tab, part);
+            part = extrap_brick<T, kAny>(args, pk, l, lds, tables, tab, part);
         if (part == 0) e += rg.stride;
     }
 }
@@ -1683,7 +1772,7 @@ __device__ int band_take(BandCtl* ctl, const int* s_pref, int nl, int Lmax, int 
     return -1;
 }
 
-template <typename T>
+template <typename T, bool kAny>
 __global__ __launch_bounds__(256, 3) void k_band(Batch b, int work_bytes) {
     HIP_DYNAMIC_SHARED(double, lds_d)
     const BandLds L = band_lds(reinterpret_cast<unsigned char*>(lds_d), (size_t)work_bytes);
@@ -1765,8 +1854,9 @@ __global__ __launch_bounds__(256, 3) void k_band(Batch b, int work_bytes) {
                                         L.s_flag, L.s_lab, L.s_list, L.s_wave);
                 else
                     for (int part = 0;;) {
-                        part = extrap_brick<T>({b.solids, b.stats, b.normal_layers, b.r_s, b.r_max},
-                                               pk_uniform, p, L.work, L.tables, tab, part);
+                        part = extrap_brick<T, kAny>(
+                            {b.solids, b.stats, b.normal_layers, b.r_s, b.r_max}, pk_uniform, p,
+                            L.work, L.tables, tab, part);
                         if (part == 0) break;
                     }
             }
@@ -1852,42 +1942,48 @@ size_t band_lds_bytes(int precision) {
 int band_blocks_per_cu(int precision) {
     static const int n[2] = {
         [] {
-            int v = 0;
-            return hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k_band<double>, 256,
-                                                                band_lds_bytes(0)) == hipSuccess &&
-                           v >= 1
+            int v = 0, w = 0;
+            const size_t lds = band_lds_bytes(0);
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k_band<double, false>, 256,
+                                                                lds) == hipSuccess &&
+                           hipOccupancyMaxActiveBlocksPerMultiprocessor(&w, k_band<double, true>,
+                                                                        256, lds) == hipSuccess &&
+                           v >= 1 && w >= 1
                        ? 1
                        : 0;
         }(),
         [] {
-            int v = 0;
-            return hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k_band<float>, 256,
-                                                                band_lds_bytes(1)) == hipSuccess &&
-                           v >= 1
+            int v = 0, w = 0;
+            const size_t lds = band_lds_bytes(1);
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k_band<float, false>, 256,
+                                                                lds) == hipSuccess &&
+                           hipOccupancyMaxActiveBlocksPerMultiprocessor(&w, k_band<float, true>,
+                                                                        256, lds) == hipSuccess &&
+                           v >= 1 && w >= 1
                        ? 1
                        : 0;
         }()};
     return n[precision == 1 ? 1 : 0];
 }
 
+// Forms of the fits: for r_s equal to the staged radius, and (kAny) for any r_s.
 hipError_t launch_band(const Batch& b, int precision, int blocks, hipStream_t st) {
     const size_t lds = band_lds_bytes(precision);
     const int work = (int)(lds - band_small_bytes());
-    if (precision == 1)
-        hipLaunchKernelGGL(k_band<float>, dim3(blocks), dim3(256), lds, st, b, work);
-    else
-        hipLaunchKernelGGL(k_band<double>, dim3(blocks), dim3(256), lds, st, b, work);
+    const bool any = b.r_s != kBrickHalo;
+    const auto k_band_form = precision == 1 ? (any ? k_band<float, true> : k_band<float, false>)
+                                            : (any ? k_band<double, true> : k_band<double, false>);
+    hipLaunchKernelGGL(k_band_form, dim3(blocks), dim3(256), lds, st, b, work);
     return hipGetLastError();
 }
 
 hipError_t launch_extrap(const Batch& b, int layer, int precision, int blocks,
                          hipStream_t st) {
-    if (precision == 1)
-        hipLaunchKernelGGL(k_extrap<float>, dim3(blocks), dim3(256), brick_lds_bytes(1), st, b,
-                           layer);
-    else
-        hipLaunchKernelGGL(k_extrap<double>, dim3(blocks), dim3(256), brick_lds_bytes(0), st, b,
-                           layer);
+    const size_t lds = brick_lds_bytes(precision);
+    const bool any = b.r_s != kBrickHalo;
+    const auto form = precision == 1 ? (any ? k_extrap<float, true> : k_extrap<float, false>)
+                                     : (any ? k_extrap<double, true> : k_extrap<double, false>);
+    hipLaunchKernelGGL(form, dim3(blocks), dim3(256), lds, st, b, layer);
     return hipGetLastError();
 }
 
