@@ -621,8 +621,14 @@ __global__ __launch_bounds__(256, 3) void k_blur_stress(BlurBatch b) {
                         for (int c = 0; c < 6; ++c)
                             out[c * pf] = sum == -1.0 ? w * tau[c] : out[c * pf] + w * tau[c];
                     } else {
+                        double v[6];
 #pragma unroll
-                        for (int c = 0; c < 6; ++c) out[c * pf] = w * tau[c];
+                        for (int c = 0; c < 6; ++c) v[c] = w * tau[c];
+                        if (w > 1.0)   // by rounding, close to phi = -eps
+#pragma unroll
+                            for (int c = 0; c < 6; ++c) v[c] = v[c] / w;
+#pragma unroll
+                        for (int c = 0; c < 6; ++c) out[c * pf] = v[c];
                     }
                 }
             }
