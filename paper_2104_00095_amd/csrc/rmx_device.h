@@ -892,48 +892,5 @@ __device__ __forceinline__ void gather_any(const CellCtx& cx, int r, bool use_no
     }
 }
 
-// Unnormalised gradient of phi0(xi) at box cell (i, j, k) of `f` (SI, weighting scheme):
-// central differences over the face neighbours where both are defined and inside the
-// box, else one-sided with the cell itself (forward first), else 0.  The seven cells are
-// loaded unconditionally (clamped into the box) before any use.
-__device__ __forceinline__ void normal_at(const ShapeR& sh, const double* __restrict__ f,
-                                          int64_t nc, int n0, int n1, int n2, int32_t cell,
-                                          int i, int j, int k, double g[3]) {
-    bool in[7];
-    int64_t cc[7];
-    in[0] = true;
-    cc[0] = cell;
-    in[1] = i + 1 < n0; cc[1] = in[1] ? cell + 1 : cell;
-    in[2] = i > 0;      cc[2] = in[2] ? cell - 1 : cell;
-    in[3] = j + 1 < n1; cc[3] = in[3] ? cell + n0 : cell;
-    in[4] = j > 0;      cc[4] = in[4] ? cell - n0 : cell;
-    in[5] = k + 1 < n2; cc[5] = in[5] ? cell + (int64_t)n0 * n1 : cell;
-    in[6] = k > 0;      cc[6] = in[6] ? cell - (int64_t)n0 * n1 : cell;
-    double x0[7], x1[7], x2[7];
-#pragma unroll
-    for (int q = 0; q < 7; ++q) {
-        x0[q] = f[cc[q]];
-        x1[q] = f[nc + cc[q]];
-        x2[q] = f[2 * nc + cc[q]];
-    }
-    double ph[7];
-    bool def[7];
-#pragma unroll
-    for (int q = 0; q < 7; ++q) {
-        def[q] = in[q] && finite3(x0[q], x1[q], x2[q]);
-        ph[q] = def[q] ? phi0(sh, x0[q], x1[q], x2[q]) : 0.0;
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const int qp = 1 + 2 * a, qm = 2 + 2 * a;
-        double ga;
-        if (def[qp] && def[qm]) ga = 0.5 * (ph[qp] - ph[qm]);
-        else if (def[qp] && def[0]) ga = ph[qp] - ph[0];
-        else if (def[qm] && def[0]) ga = ph[0] - ph[qm];
-        else ga = 0.0;
-        g[a] = ga;
-    }
-}
-
 }  // namespace dev
 }  // namespace rmx
