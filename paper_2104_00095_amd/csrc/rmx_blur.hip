@@ -145,10 +145,12 @@ __global__ __launch_bounds__(256) void k_blur_scan(BlurBatch b) {
 // its faces along an axis: ext_a + 1 of them along a, at most n on a periodic axis) is cut
 // into units, a wave each: 8192 consecutive values where the region spans whole planes of
 // the array (16-byte stores), else 16 rows along x of one plane.  Bound by the stores where
-// planes are whole: 2.4 GB of stress zeros of one 256^3 box 409 us (5.9 TB/s; a row along x
-// per wave 469 us).  The runs bypass the caches (427 us otherwise: they hold nothing of use
-// to the next kernel); the rows of small boxes do not (235 against 136 us for 376 MB on 40
-// boxes: a row's ends share cache lines with cells outside the box).
+// planes are whole: 2.4 GB of stress zeros of one 256^3 box 418 us (5.8 TB/s; a row along x
+// per wave 469 us).  The runs bypass the caches, since they hold nothing of use to the next
+// kernel: through the caches 434 us (435 against 407 on arrays written for the first time, 433
+// against 416 on four sets of arrays in turn), and the stress kernel behind it 107 us against 99.
+// The rows of small boxes go through the caches (136 us for 376 MB on 40 boxes; bypassing them
+// 235: a row's ends share cache lines with cells outside the box).
 // ------------------------------------------------------------------------------------
 __device__ __forceinline__ int fill_extent(const BlurBatch& b, BlurDevC* s, int a, int ax) {
     const int e = s->ext[ax] + (ax == a ? 1 : 0);
@@ -257,9 +259,10 @@ __device__ __forceinline__ int list_cells(unsigned bits, int lane, uint16_t* lis
 // cells first, so each thread takes two cells of the tile and visits the candidates.
 // Otherwise the covered cells of a tile are listed by one wave; the certificates decide most
 // weights; the cells they leave are listed again, so that the exact distances (a bisection)
-// run in full waves.  Measured: 40 ellipsoids 95 -> 44 us (81 us with a bisection of each
-// point; bound by the chain of the distance); 8 spheres in 256^3 16.6 -> 15.6 us (the listed
-// form took 27 us there).
+// run in full waves.  Measured: 40 ellipsoids 95 -> 44 us without phi in a loop of calls (81 us
+// with a bisection of each point; 50 to 52 us where each call is waited for, 54 to 56 with phi;
+// bound by the chain of the distance, 28 bytes of scratch); one sphere in 256^3 16.6 -> 15.6 us
+// with phi (the listed form took 27 us there).
 __global__ __launch_bounds__(256) void k_blur_heaviside_spheres(BlurBatch b) {
     const int tid = threadIdx.x;
     const int images = b.periodic[0] || b.periodic[1] || b.periodic[2] ? 8 : 1;
@@ -449,7 +452,7 @@ __device__ __forceinline__ unsigned face_bits(const unsigned* rows, int a, int y
 // where several do, they add up in tau in ascending order, and the sums with
 // S > 1 are divided at the end.  Bound by instructions and by the latency of each tile's
 // chain (labels, list, xi, faces).  Measured: 40 ellipsoids in 128x128x256 420 -> 120 us,
-// 8 spheres in 256^3 159 -> 93 us (before: an 8^3 tile's faces on all threads, ten label
+// one sphere in 256^3 159 -> 98 us (before: an 8^3 tile's faces on all threads, ten label
 // bytes and thirty xi loads per face, the bisection of the distance in sparse waves).
 template <bool kSpheres>
 __global__ __launch_bounds__(256, 3) void k_blur_stress(BlurBatch b) {

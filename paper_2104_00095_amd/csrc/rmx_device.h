@@ -342,8 +342,9 @@ __device__ __forceinline__ double div_near(double a, double b, double y) {
 // f goes from positive to negative: if that is between adjacent numbers, or at a single 0
 // between them, it ends there whatever its path.  f at the seven numbers around a Newton
 // estimate of the root (steps in single precision, then in double, then one on the computed f
-// itself; reciprocals refined from one number to the next) settles it for most points.  A run of zeros is entered at the first midpoint that falls on it: those points
-// follow the path, from the whole bracket, by comparisons with the run's ends alone.
+// itself; reciprocals refined from one number to the next) settles it for most points.  A run
+// of zeros is entered at the first midpoint that falls on it: those points follow the path, from
+// the whole bracket, by comparisons with the run's ends alone.
 // Returns false, with nothing computed, for coordinates of 0, magnitudes far from 1, and where
 // 27 numbers on one side do not hold the change of sign.
 // Bound by the latency of the chain (a wave's points take it together): 5.3 us for a wave's

@@ -39,8 +39,8 @@ constexpr int kBrick = 8;
 constexpr int kBrickHalo = 2;
 constexpr int kBrickSpan = kBrick + 2 * kBrickHalo;                // 12
 // Staged cells of a brick at most: in FP32 the whole region, in FP64 what lets four blocks per
-// CU fit the LDS.  The layers of smooth surfaces need 650 on average and up to 1250; half a
-// brick at most 1152.
+// CU fit the LDS.  The layers of smooth surfaces need 650 on average and up to 1250, those around
+// a solid of three to six cells radius up to 1680; half a brick at most 1152.
 template <typename T>
 __host__ __device__ constexpr int span_cells() {
     return sizeof(T) == 4 ? kBrickSpan * kBrickSpan * kBrickSpan : 1440;

@@ -19,8 +19,8 @@
 //               it) in LDS; a group of 4, 8 or 16 lanes per cell of the layer (as many as
 //               keep the brick's cells in one pass) gathers the (2r+1)^3 box from LDS,
 //               accumulates the 4x4 normal-equation moments, reduces them by DPP moves,
-//               decides degeneracy by an exact integer determinant, solves in FP64 and
-//               writes xi_e.
+//               decides degeneracy by the pivots where they are far from 0 and by an exact
+//               integer determinant elsewhere, solves in FP64 and writes xi_e.
 // The work is bandwidth- and latency-bound, with 4x4 systems per cell: no MFMA.
 #include "rmx_device.h"
 
@@ -1938,7 +1938,8 @@ size_t band_lds_bytes(int precision) {
 // Blocks per CU of the persistent launch: one, when one fits.  Each block releases (an L2
 // write-back of its XCD) when it leaves a phase and acquires (an L2 invalidation) when it
 // enters one; with more blocks per CU these operations thrash the L2 more than the added
-// residency hides latency (one block per CU measured twice as fast as three).
+// residency hides latency (with the fits of before the row bits, a 256^3 sphere's launch took
+// 384 us with one block per CU and 790 with three; the call takes 416 us now).
 int band_blocks_per_cu(int precision) {
     static const int n[2] = {
         [] {

@@ -309,7 +309,7 @@ __device__ void trans_segment(const StepBatch& b, int64_t w) {
             // only the expansion the sign of wv selects: from x up, or from x + s down (both
             // where it is 0).  One form for both signs, and the stores after the axis' loads
             // (the compiler keeps them in order), so that all components' loads are in flight
-            // together (16 spheres 30 -> 28 us, 8 spheres in 256^3 52.5 -> 51).
+            // together (16 spheres 30 -> 28 us, one sphere in 256^3 52.5 -> 51).
             const int64_t from = wv < 0.0 ? x + s : x;
             const double coef = wv < 0.0 ? -(0.5 + hl * vy) : 0.5 - hl * vx;
             double chosen[3];
@@ -373,7 +373,7 @@ __device__ void faces_segment(const StepBatch& b, int64_t w) {
     const int64_t nc = d->ncell;
     // Bound by the latency of its loads (173 MB, 2.3 TB/s on 700 000 cells with 8 waves per
     // SIMD resident): every label and face velocity that decides is loaded before the first is
-    // used (16 spheres 37 -> 34 us, 8 spheres in 256^3 77 -> 76).  An axis' loads all ahead of
+    // used (16 spheres 37 -> 34 us, one sphere in 256^3 77 -> 76).  An axis' loads all ahead of
     // its stores take 76 registers and gave up more waves than they gained (79 us).
     const bool self = predicted(sd, d, g.i, g.j, g.k);
     bool his[3], los[3];
