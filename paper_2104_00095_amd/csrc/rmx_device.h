@@ -530,19 +530,21 @@ __device__ __forceinline__ void block_scan(int v, int& excl, int& total, int* s_
     __syncthreads();
 }
 
-// Entries [0, count) of a list, split into one contiguous range per XCD in proportion to its
-// blocks (workgroups are dealt to the XCDs round-robin): neighbouring entries, whose halos
-// overlap, are then fetched into one L2, and no block takes more than ceil(count / blocks)
-// entries.  (Equal ranges give some blocks of a grid that is no multiple of 8 an entry too
-// many: a lone 24^3 box, 27 blocks, 75 us per call against 60.)  The calling block takes begin,
-// begin + stride, ... below end.
+// Entries [0, count) of a list, split into one contiguous range per XCD (workgroups are dealt to
+// the XCDs round-robin): neighbouring entries, whose halos overlap, are then fetched into one L2,
+// and no block takes more than ceil(count / blocks) entries.  The ranges are equal where that
+// holds for them, and in proportion to the XCDs' blocks elsewhere: equal ranges would give some
+// blocks of a grid that is no multiple of 8 an entry too many (a lone 24^3 box, 27 blocks, 75 us
+// per call against 60), and the other form costs short kernels more than its divisions (stress
+// of 27 overlapping boxes, 290 tiles on 343 blocks, 113 us against 104).  The calling block takes
+// begin, begin + stride, ... below end.
 struct XcdRange {
     int begin, end, stride;
 };
 __device__ __forceinline__ XcdRange xcd_range(int count) {
     const int G = gridDim.x, b = blockIdx.x;
     const int x = b % kXcds;
-    if (G % kXcds == 0) {   // the XCDs have the same number of blocks (no division by G)
+    if (G % kXcds == 0 || count <= G - G % kXcds) {   // as many blocks each, or one entry a block
         const int per = (count + kXcds - 1) / kXcds;
         return {x * per + b / kXcds, min(count, (x + 1) * per), G / kXcds};
     }
