@@ -263,10 +263,12 @@ __device__ __forceinline__ int list_cells(unsigned bits, int lane, uint16_t* lis
 // cells first, so each thread takes two cells of the tile and visits the candidates.
 // Otherwise the covered cells of a tile are listed by one wave; the certificates decide most
 // weights; the cells they leave are listed again, so that the exact distances (a bisection)
-// run in full waves.  Measured: 40 ellipsoids 95 -> 44 us without phi in a loop of calls (81 us
-// with a bisection of each point; 50 to 52 us where each call is waited for, 54 to 56 with phi;
-// bound by the chain of the distance, 28 bytes of scratch); one sphere in 256^3 16.6 -> 15.6 us
-// with phi (the listed form took 27 us there).
+// run in full waves.  256 threads a tile: the chain of the distance binds, and its rounds over a
+// tile count (with 128 threads 50 us instead of 47 for 40 ellipsoids, 62 instead of 48 for phi of
+// a 128^3 box; 512 threads, with phi: the call 100 us against 90 on the 40, 73 against 79 on the
+// box).  Measured: 40 ellipsoids 95 -> 47 us without phi (81 with a bisection of each
+// point), 49 with phi (28 bytes of scratch); one sphere in 256^3 16.6 -> 15.6 us with phi (the
+// listed form took 27 us there).
 __global__ __launch_bounds__(256) void k_blur_heaviside_spheres(BlurBatch b) {
     const int tid = threadIdx.x;
     const int images = b.periodic[0] || b.periodic[1] || b.periodic[2] ? 8 : 1;
@@ -319,7 +321,7 @@ __global__ __launch_bounds__(256) void k_blur_heaviside_spheres(BlurBatch b) {
     }
 }
 
-constexpr int kHeavisideThreads = 128;
+constexpr int kHeavisideThreads = 256;
 
 __global__ __launch_bounds__(kHeavisideThreads, 4) void k_blur_heaviside(BlurBatch b) {
     __shared__ double s_acc[kBlurTileCells];
