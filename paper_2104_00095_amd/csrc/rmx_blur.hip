@@ -147,9 +147,9 @@ __global__ __launch_bounds__(256) void k_blur_scan(BlurBatch b) {
 // the array (16-byte stores), else 16 rows along x of one plane.  Bound by the stores where
 // planes are whole: 2.4 GB of stress zeros of one 256^3 box 418 us (5.8 TB/s; a row along x
 // per wave 469 us).  The runs bypass the caches, since they hold nothing of use to the next
-// kernel: through the caches 434 us (435 against 407 on arrays written for the first time, 433
-// against 416 on four sets of arrays in turn), and the stress kernel behind it 107 us against 99.
-// The rows of small boxes go through the caches (136 us for 376 MB on 40 boxes; bypassing them
+// kernel: through the caches 434 us (426 against 415 on arrays written for the first time, 436
+// against 421 on four sets of arrays in turn), and the stress kernel behind it 107 us against 100.
+// The rows of small boxes go through the caches (127 us for 376 MB on 40 boxes; bypassing them
 // 235: a row's ends share cache lines with cells outside the box).
 // ------------------------------------------------------------------------------------
 __device__ __forceinline__ int fill_extent(const BlurBatch& b, BlurDevC* s, int a, int ax) {
